@@ -232,27 +232,16 @@ int hip_fail(kkm_ctx* c, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(c, e_, what); \
   } while (0)
 
-// K, and the iteration scratch the SpMM reads its chunk tables from and
-// writes its partial sums into, are allocated as physically contiguous memory
-// when K is at least this large (hipMalloc is the fallback).  With K of 7 GB
-// and more, the packed SpMM measured 3.6% faster (60000 points) and 6% faster
-// (200000 points) with a contiguous scratch than with one from hipMalloc, on
-// the same K, and the full-K SpMM 0.6-2%; with K of 1.6 GB and less it
-// measured 0.5-7% slower, so small problems keep hipMalloc.
-constexpr size_t kContiguousFromK = (size_t)4 << 30;
-
-int dalloc(kkm_ctx* c, void** p, size_t bytes, std::vector<Alloc>& owner, const char* what,
-           bool contiguous = false) {
+// Every buffer is plain hipMalloc memory.  Physically contiguous allocations
+// (hipDeviceMallocContiguous) for a K of 4 GB and more measured 0-1.5% faster
+// per update, but memory allocated after such a buffer had been freed held
+// stale lines in some XCDs' L2: a K build on it came out wrong in places.
+int dalloc(kkm_ctx* c, void** p, size_t bytes, std::vector<Alloc>& owner, const char* what) {
   bytes = std::max<size_t>(bytes, 256);
   if (c->held + bytes > c->budget)
     return fail(c, KKM_ERR_OOM, "%s needs %zu bytes; %zu of the %zu-byte budget already held", what,
                 bytes, c->held, c->budget);
-  hipError_t e = hipErrorOutOfMemory;
-  if (contiguous) {
-    e = hipExtMallocWithFlags(p, bytes, hipDeviceMallocContiguous);
-    if (e != hipSuccess) (void)hipGetLastError();
-  }
-  if (e != hipSuccess) e = hipMalloc(p, bytes);
+  hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -498,8 +487,7 @@ int release_fix_list(kkm_ctx* c) {
 // Allocate one block and carve it (keeps the accounting to one number).
 int carve_ws(kkm_ctx* c, int k) {
   void* base = nullptr;
-  int rc = dalloc(c, &base, ws_bytes(c->wsz, k, c->mode), c->ws_allocs, "iteration scratch",
-                  k_bytes(c->wsz, c->mode, c->storage) >= kContiguousFromK);
+  int rc = dalloc(c, &base, ws_bytes(c->wsz, k, c->mode), c->ws_allocs, "iteration scratch");
   if (rc) return rc;
   return carve_from(c, k, base);
 }
@@ -844,7 +832,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     const bool stores_k = mode == KKM_MODE_RESIDENT || mode == KKM_MODE_PACKED;
     if (stores_k) {
       const size_t kb = k_bytes(c->wsz, mode, storage);
-      if ((rc = dalloc(c, &p, kb, c->build_allocs, "kernel matrix K", kb >= kContiguousFromK))) return rc;
+      if ((rc = dalloc(c, &p, kb, c->build_allocs, "kernel matrix K"))) return rc;
       c->K = p;
     }
     if (row_scaled(mode, storage, kind)) {
