@@ -180,6 +180,11 @@ struct kkm_ctx {
   long long fix_cap = 0;                    // entries in all segments together
   int64_t fixups = 0;
   std::vector<Alloc> build_allocs;
+  // The split points (split_mma.h) the K build takes where memory allows, and
+  // gives back when something else needs the room; null: the fp32 build.
+  half_t* Xf = nullptr;
+  float* xinv = nullptr;
+  std::vector<Alloc> split_allocs;
 
   int k_ws = 0, iter_ws = 0;
   IterBufs ib{};
@@ -236,12 +241,35 @@ int hip_fail(kkm_ctx* c, hipError_t e, const char* what) {
 // (hipDeviceMallocContiguous) for a K of 4 GB and more measured 0-1.5% faster
 // per update, but memory allocated after such a buffer had been freed held
 // stale lines in some XCDs' L2: a K build on it came out wrong in places.
+void release(kkm_ctx* c, std::vector<Alloc>& owner) {
+  for (const Alloc& a : owner) {
+    (void)hipFree(a.p);
+    c->held -= std::min(c->held, a.bytes);
+  }
+  owner.clear();
+}
+
+// The split points serve the K build only; later builds make them again.
+void release_split(kkm_ctx* c) {
+  if (!c->Xf) return;
+  (void)hipStreamSynchronize(c->stream);
+  release(c, c->split_allocs);
+  c->Xf = nullptr;
+  c->xinv = nullptr;
+}
+
 int dalloc(kkm_ctx* c, void** p, size_t bytes, std::vector<Alloc>& owner, const char* what) {
   bytes = std::max<size_t>(bytes, 256);
+  if (c->held + bytes > c->budget && c->Xf) release_split(c);
   if (c->held + bytes > c->budget)
     return fail(c, KKM_ERR_OOM, "%s needs %zu bytes; %zu of the %zu-byte budget already held", what,
                 bytes, c->held, c->budget);
   hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && c->Xf) {  // once more without the split points
+    (void)hipGetLastError();
+    release_split(c);
+    e = hipMalloc(p, bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -250,14 +278,6 @@ int dalloc(kkm_ctx* c, void** p, size_t bytes, std::vector<Alloc>& owner, const 
   owner.push_back({*p, bytes});
   c->held += bytes;
   return KKM_OK;
-}
-
-void release(kkm_ctx* c, std::vector<Alloc>& owner) {
-  for (const Alloc& a : owner) {
-    (void)hipFree(a.p);
-    c->held -= std::min(c->held, a.bytes);
-  }
-  owner.clear();
 }
 
 hipEvent_t take_event(kkm_ctx* c) {
@@ -329,6 +349,7 @@ void free_build(kkm_ctx* c) {
   free_ws(c);
   free_hist(c);
   free_seed(c);
+  release_split(c);
   release(c, c->build_allocs);
   c->Xp = c->nrm = c->diagK = c->bmax = nullptr;
   c->K = nullptr;
@@ -856,10 +877,29 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     c->fix_count = (unsigned long long*)((char*)p + (size_t)cap * sizeof(int2));
     c->fix_cap = cap;
   }
+  // The split points, where the budget holds them beside the iteration scratch.
+  const bool f16 = storage == KKM_STORE_F16;
+  const bool splits = mode != KKM_MODE_ONTHEFLY && (panel || f16 || s.d_pad > kRegMaxDpad);
+  if (splits && !c->Xf) {
+    const size_t bytes = split_bytes(s.n_pad, s.d_pad);
+    const int32_t kh = std::min<int64_t>(params->k_hint, n);
+    const size_t scratch = c->ws_allocs.empty() ? ws_bytes(c->wsz, kh > 0 ? kh : 1, mode) + 4096 : 0;
+    if (c->held + bytes + scratch <= c->budget) {
+      if (hipMalloc(&p, bytes) == hipSuccess) {
+        c->split_allocs.push_back({p, bytes});
+        c->held += bytes;
+        c->Xf = (half_t*)p;
+        c->xinv = (float*)((char*)p + (bytes - (size_t)split_rows(s.n_pad) * 4));
+      } else {
+        (void)hipGetLastError();
+      }
+    }
+  }
+  const SplitPoints sp{c->Xf, c->xinv, split_rows(s.n_pad), (s.d_pad + 15) / 16};
   if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, 1, c->stream); })))
     return rc;
   if ((rc = run(c, KKM_PHASE_STAGE, "stage", [&] {
-         return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, c->stream);
+         return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, c->Xf, c->xinv, sp.rows, c->stream);
        })))
     return rc;
   c->fixups = -1;  // read from the device on demand
@@ -874,7 +914,6 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
       return rc;
     return run(c, KKM_PHASE_OTHER, "trace", [&] { return launch_trace(c->diagK, n, c->trK, c->stream); });
   }
-  const bool f16 = storage == KKM_STORE_F16;
   if (c->kw && (rc = run(c, KKM_PHASE_STAGE, "row_scales", [&] {
         return launch_row_scales(c->nrm, c->maxnrm, n, kp, c->kw, c->stream);
       })))
@@ -882,15 +921,26 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   if (!panel && kind == KKM_GAUSS &&
       (rc = run(c, KKM_PHASE_STAGE, "blockmax", [&] { return launch_blockmax(c->nrm, s.n_pad / kTile, c->bmax, c->stream); })))
     return rc;
-  if ((rc = run(c, KKM_PHASE_GEMM, "gemm_kappa", [&] {
+  if (c->Xf && (rc = run(c, KKM_PHASE_GEMM, "gemm_split", [&] {
+        if (panel)
+          return launch_gemm_split_panel(sp, c->nrm, c->maxnrm, n, pr0, pr1, pc0, pc1, s.ld, kp, (float*)c->K,
+                                         c->diagK, c->fix_list, c->fix_count, c->fix_cap / kFixSegs, c->stream);
+        return launch_gemm_split(sp, c->nrm, c->maxnrm, n, s.ld, mode == KKM_MODE_PACKED, f16,
+                                 f16 ? c->kw : nullptr, kp, c->K, c->diagK, c->fix_list, c->fix_count,
+                                 c->fix_cap / kFixSegs, kind == KKM_GAUSS ? c->bmax : nullptr, c->stream);
+      })))
+    return rc;
+  // without the split points, and for a norm past fp32's range (read on the device)
+  const bool only_inf = c->Xf != nullptr;
+  if ((rc = run(c, only_inf ? KKM_PHASE_OTHER : KKM_PHASE_GEMM, "gemm_kappa", [&] {
          if (panel)
            return launch_gemm_kappa_panel(c->Xp, c->nrm, c->maxnrm, n, s.d_pad, pr0, pr1, pc0, pc1, s.ld, kp,
                                           (float*)c->K, c->diagK, c->fix_list, c->fix_count,
-                                          c->fix_cap / kFixSegs, c->stream);
+                                          c->fix_cap / kFixSegs, only_inf, c->stream);
          // the build divides by the row bounds only for binary16 storage
          return launch_gemm_kappa(c->Xp, c->nrm, c->maxnrm, n, s.d_pad, s.ld, mode == KKM_MODE_PACKED, f16,
                                   f16 ? c->kw : nullptr, kp, c->K, c->diagK, c->fix_list, c->fix_count,
-                                  c->fix_cap / kFixSegs, c->bmax, c->stream);
+                                  c->fix_cap / kFixSegs, c->bmax, only_inf, c->stream);
        })))
     return rc;
   if (kind == KKM_GAUSS &&

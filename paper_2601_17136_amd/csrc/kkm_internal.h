@@ -24,6 +24,9 @@ constexpr int64_t kMaxKStride = (int64_t)1 << 23;
 constexpr int kStripe = 1024;
 constexpr int kChunk = 1024;
 
+// The sweep kernels of small widths take d_pad up to this.
+constexpr int kRegMaxDpad = 64;
+
 // Points per workgroup in the label/assign/scatter kernels.
 constexpr int kBlk = 256;
 
@@ -57,6 +60,9 @@ inline int sym_seg_for(int64_t n, int k) {
   if (n <= kSymLargeN) return k <= 16 ? 16 : 32;
   return k <= 16 ? 16 : 64;
 }
+// Split build: 256 x 128 workgroup tiles from this many 128 x 128 tiles up
+// (counting both halves of a square layout's grid), 128 x 128 below.
+constexpr int64_t kSplitTallTiles = 2048;
 constexpr int kSymMaxK = 64;
 constexpr int kSymRedStripe = 256;  // columns per workgroup of the packed reduction
 
@@ -76,6 +82,9 @@ inline int64_t packed_floats(int64_t n, int64_t ld) { return packed_row(n - 1, l
 // each; workgroup b appends to segment b % kFixSegs, so no single atomic
 // counter serialises the K build.
 constexpr int kFixSegs = 256;
+
+// binary16 storage of K, split points
+typedef _Float16 half_t;
 
 enum Kind { LINEAR = 0, POLY = 1, GAUSS = 2 };
 
@@ -138,12 +147,33 @@ struct IterBufs {
   const float* kw;
 };
 
-// binary16 storage of K
-typedef _Float16 half_t;
-
 // ---------------------------------------------------------------- launchers
-hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp,
-                        float* nrm, unsigned* maxnrm_bits, hipStream_t s);
+// Xf (may be null): also the split points of n_split rows, see split_mma.h
+hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
+                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, int64_t n_split, hipStream_t s);
+// The split points (split_mma.h): rows a multiple of 32, nch = ceil(d_pad / 16).
+struct SplitPoints {
+  const half_t* Xf;
+  const float* xinv;
+  int64_t rows;
+  int nch;
+};
+// rows of the split points: a 256-row workgroup may reach one tile past n_pad
+inline int64_t split_rows(int64_t n_pad) { return n_pad + kTile; }
+inline size_t split_bytes(int64_t n_pad, int d_pad) {
+  return (size_t)split_rows(n_pad) * ((size_t)((d_pad + 15) / 16) * 64 + 4);
+}
+// launch_gemm_kappa and launch_gemm_kappa_panel from the split points; they
+// build nothing when the largest squared norm is not finite (those launch
+// beside them with only_inf set).
+hipError_t launch_gemm_split(const SplitPoints& sp, const float* nrm, const unsigned* maxnrm_bits, int64_t n,
+                             int64_t ld, bool packed, bool f16, const float* kw, const KappaParams& kp, void* K,
+                             float* diagK, int2* fix_list, unsigned long long* fix_count, long long seg_cap,
+                             const float* bmax, hipStream_t s);
+hipError_t launch_gemm_split_panel(const SplitPoints& sp, const float* nrm, const unsigned* maxnrm_bits, int64_t n,
+                                   int64_t r0, int64_t r1, int64_t c0, int64_t c1, int64_t ld, const KappaParams& kp,
+                                   float* K, float* diagK, int2* fix_list, unsigned long long* fix_count,
+                                   long long seg_cap, hipStream_t s);
 // Row scales of binary16 storage: kw[i] bounds |K(i, j)| for every j
 // (from the row norms and the largest one; linear and polynomial kernels).
 hipError_t launch_row_scales(const float* nrm, const unsigned* maxnrm_bits, int64_t n, const KappaParams& kp,
@@ -154,11 +184,14 @@ hipError_t launch_row_scales(const float* nrm, const unsigned* maxnrm_bits, int6
 // (n_pad entries, zero past n), one per 128-point block
 hipError_t launch_blockmax(const float* nrm, int64_t nblocks, float* bmax, hipStream_t s);
 // bmax: the block maxima of nrm (launch_blockmax), read by the small-width
-// sweep for the Gaussian kernel (may be null otherwise)
+// sweep for the Gaussian kernel (may be null otherwise).
+// only_inf: a small launch that builds K only when the largest squared norm
+// is not finite (beside launch_gemm_split, which then does nothing)
 hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,
                              int64_t n, int d_pad, int64_t ld, bool packed, bool f16, const float* kw,
                              const KappaParams& kp, void* K, float* diagK, int2* fix_list,
-                             unsigned long long* fix_count, long long seg_cap, const float* bmax, hipStream_t s);
+                             unsigned long long* fix_count, long long seg_cap, const float* bmax, bool only_inf,
+                             hipStream_t s);
 // Recomputes the listed Gaussian entries (counts read on the device); if a
 // segment received more entries than it holds, re-tests the whole triangle.
 // fix_list holds kFixSegs segments of seg_cap entries; fix_count kFixSegs counters.
@@ -175,7 +208,7 @@ hipError_t launch_gauss_fixup(const float* Xp, const float* nrm, int64_t n, int 
 hipError_t launch_gemm_kappa_panel(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,
                                    int64_t n, int d_pad, int64_t r0, int64_t r1, int64_t c0, int64_t c1,
                                    int64_t ld, const KappaParams& kp, float* K, float* diagK, int2* fix_list,
-                                   unsigned long long* fix_count, long long seg_cap, hipStream_t s);
+                                   unsigned long long* fix_count, long long seg_cap, bool only_inf, hipStream_t s);
 // D and lowest-index argmin for the panel's points (columns [b.col0, b.col0 + b.ncol))
 // from E^T (k x ld, column = point - col0), the global z and the cluster sizes;
 // counts_out gets the panel's share of the new sizes (added; zeroed by the caller).

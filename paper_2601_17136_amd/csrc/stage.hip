@@ -5,51 +5,77 @@
 // need bounds checks along k; zero columns leave every dot product, and so
 // Eq. 1, unchanged.  The squared row norms |x_i|^2 are taken in the same pass
 // (the Gaussian kernel's expansion |x|^2 + |y|^2 - 2 x.y needs them).
-#include "kkm_internal.h"
+#include "split_mma.h"
 
 namespace kkm {
 
-// Each wavefront stages kStageRows rows at once (their loads in flight
-// together); per row, lane l sums the squares of columns l, l+64, ... in order
-// and a fixed shuffle tree adds the lanes, so the norm is deterministic.
-// maxnrm_bits (zero on entry) receives the largest norm as its IEEE bits
-// (non-negative floats order like their bit patterns); a workgroup takes the
-// max of its rows in LDS and updates the word only when its max is larger than
-// what the word already holds.  A stale read only costs a redundant atomic.
+// A workgroup stages kStageBlk rows, each wavefront kStageRows at once (their
+// loads in flight together); per row, lane l sums the squares of columns l,
+// l+64, ... in order and a fixed shuffle tree adds the lanes, so the norm is
+// deterministic.  maxnrm_bits (zero on entry) receives the largest norm as its
+// IEEE bits (non-negative floats order like their bit patterns); a workgroup
+// takes the max of its rows in LDS and updates the word only when its max is
+// larger than what the word already holds.  A stale read only costs a
+// redundant atomic.
+//
+// Xf (may be null): the split points in operand order (split_mma.h), n_split
+// rows (a multiple of kStageBlk; rows past n are zero), and xinv[i] = 1 / s_i,
+// the power of two that undoes row i's scale.  The rows' largest coordinates
+// come from the same pass as the norms, and the second pass reads the staged
+// rows back from cache.
 constexpr int kStageRows = 4;
 constexpr int kStageWaves = 4;
+constexpr int kStageBlk = 32;
 
 __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __restrict__ X, int64_t n,
                                                                  int d, int d_pad, int64_t n_pad,
                                                                  float* __restrict__ Xp,
                                                                  float* __restrict__ nrm,
-                                                                 unsigned* __restrict__ maxnrm_bits) {
+                                                                 unsigned* __restrict__ maxnrm_bits,
+                                                                 half_t* __restrict__ Xf,
+                                                                 float* __restrict__ xinv) {
   __shared__ float wmax[kStageWaves];
+  __shared__ float scl[kStageBlk];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t i0 = ((int64_t)blockIdx.x * kStageWaves + w) * kStageRows;
-  float s[kStageRows];
-#pragma unroll
-  for (int r = 0; r < kStageRows; ++r) s[r] = 0.f;
-  for (int c = lane; c < d_pad; c += 64) {
-    float v[kStageRows];
-#pragma unroll
-    for (int r = 0; r < kStageRows; ++r) {
-      const int64_t i = i0 + r;
-      v[r] = (i < n && c < d) ? X[i * d + c] : 0.f;
-    }
-#pragma unroll
-    for (int r = 0; r < kStageRows; ++r) {
-      const int64_t i = i0 + r;
-      if (i < n_pad) Xp[i * d_pad + c] = v[r];
-      s[r] = fmaf(v[r], v[r], s[r]);
-    }
-  }
+  const int64_t b0 = (int64_t)blockIdx.x * kStageBlk;
   float m = 0.f;
+  for (int g = 0; g < kStageBlk / (kStageRows * kStageWaves); ++g) {
+    const int64_t i0 = b0 + (g * kStageWaves + w) * kStageRows;
+    float s[kStageRows], mx[kStageRows];
 #pragma unroll
-  for (int r = 0; r < kStageRows; ++r) {
-    for (int off = 32; off > 0; off >>= 1) s[r] += __shfl_xor(s[r], off, 64);
-    if (lane == r && i0 + r < n_pad) nrm[i0 + r] = s[r];
-    m = fmaxf(m, s[r]);
+    for (int r = 0; r < kStageRows; ++r) s[r] = mx[r] = 0.f;
+    for (int c = lane; c < d_pad; c += 64) {
+      float v[kStageRows];
+#pragma unroll
+      for (int r = 0; r < kStageRows; ++r) {
+        const int64_t i = i0 + r;
+        v[r] = (i < n && c < d) ? X[i * d + c] : 0.f;
+      }
+#pragma unroll
+      for (int r = 0; r < kStageRows; ++r) {
+        const int64_t i = i0 + r;
+        if (i < n_pad) Xp[i * d_pad + c] = v[r];
+        s[r] = fmaf(v[r], v[r], s[r]);
+        mx[r] = fmaxf(mx[r], fabsf(v[r]));
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kStageRows; ++r) {
+      for (int off = 32; off > 0; off >>= 1) {
+        s[r] += __shfl_xor(s[r], off, 64);
+        mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], off, 64));
+      }
+      if (lane == r && i0 + r < n_pad) nrm[i0 + r] = s[r];
+      if (lane == r && Xf) {
+        // s_i = 2^(14 - e) for a largest coordinate in [2^e, 2^(e+1)), at most
+        // 2^126; 1 for a zero row and for one that holds an infinity
+        const int e = max((int)(__float_as_uint(mx[r]) >> 23), 1) - 127;
+        const int p = mx[r] > 0.f && mx[r] < INFINITY ? min(14 - e, 126) : 0;
+        scl[i0 + r - b0] = __uint_as_float((unsigned)(127 + p) << 23);
+        xinv[i0 + r] = __uint_as_float((unsigned)(127 - p) << 23);
+      }
+      m = fmaxf(m, s[r]);
+    }
   }
   if (lane == 0) wmax[w] = m;
   __syncthreads();
@@ -59,14 +85,37 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
     if (__hip_atomic_load(maxnrm_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < bits)
       atomicMax(maxnrm_bits, bits);
   }
+  if (!Xf) return;
+  const int nch = (d_pad + 15) / 16, l = lane & 31, h = lane >> 5;
+  const float sc = scl[l];
+  const float* row = Xp + (b0 + l) * d_pad + 8 * h;
+  for (int c = w; c < nch; c += kStageWaves) {
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (b0 < n_pad && 16 * c + 8 * h < d_pad) {  // n_pad and d_pad are multiples of the block and of 8
+      const float4 x0 = *(const float4*)(row + 16 * c), x1 = *(const float4*)(row + 16 * c + 4);
+      v[0] = x0.x, v[1] = x0.y, v[2] = x0.z, v[3] = x0.w;
+      v[4] = x1.x, v[5] = x1.y, v[6] = x1.z, v[7] = x1.w;
+    }
+    half8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float x = v[e] * sc;
+      hi[e] = (half_t)x;
+      lo[e] = (half_t)(x - (float)hi[e]);
+    }
+    half_t* u = Xf + split_unit(blockIdx.x, nch, c, 0) * kUnit + lane * 8;
+    *(half8*)u = hi;
+    *(half8*)(u + kUnit) = lo;
+  }
 }
 
-hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp,
-                        float* nrm, unsigned* maxnrm_bits, hipStream_t s) {
-  const int64_t rows = (int64_t)kStageRows * kStageWaves;
-  dim3 grid((unsigned)((n_pad + rows - 1) / rows));
+hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
+                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, int64_t n_split, hipStream_t s) {
+  const int64_t rows = Xf ? n_split : n_pad;
+  if (rows % kStageBlk || n_pad % kStageBlk || rows < n_pad) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(rows / kStageBlk));
   hipLaunchKernelGGL(stage_kernel, grid, dim3(64 * kStageWaves), 0, s, X, n, d, d_pad, n_pad, Xp, nrm,
-                     maxnrm_bits);
+                     maxnrm_bits, Xf, xinv);
   return hipGetLastError();
 }
 

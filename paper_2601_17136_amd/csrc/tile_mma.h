@@ -128,7 +128,6 @@ __device__ inline void mma_tile(const float* __restrict__ Xa, const float* __res
 // into registers: lane (l, h) holds column l of each 32-column block at
 // k = h*HP .. h*HP + HP - 1 (HP = d_pad / 2), and step s of
 // v_mfma_f32_32x32x2_f32 pairs k = s with k = HP + s.
-constexpr int kRegMaxDpad = 64;
 
 template <int HP>
 __device__ inline void load_operand(const float* __restrict__ Y, int64_t row, int d_pad, int h, float (&v)[HP]) {

@@ -1,0 +1,141 @@
+"""The K build on the binary16 matrix cores (each coordinate as two binary16 values).
+
+Sizes sit at the edges of its tiles: 128 x 128 workgroup tiles below 64 tiles a
+side, 256 x 128 above (an odd tile count leaves the last workgroup row half
+empty), ragged last rows and columns, coordinate counts below, at and above
+its chunks of 16.
+"""
+import numpy as np
+import pytest
+
+from gpu_helpers import Engine
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch_cuda():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch
+
+
+def _points(n, d, seed, spread=True):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    if spread:  # row scales over 24 binary orders, a zero row, coordinates over 12 more within a row
+        X *= np.exp2(rng.integers(-12, 13, size=(n, 1))).astype(np.float32)
+        X *= np.exp2(rng.integers(-12, 1, size=(n, d))).astype(np.float32)
+        X[n // 2] = 0.0
+    return X
+
+
+def _bound(X, d):
+    """|K - x.y| for the linear kernel: a coordinate is held to 2^-24 of itself
+    or 2^-39 of its row's largest, lo lo (2^-22 of a product) is left out, and
+    the fp32 sum is rounded three times per 16 coordinates and once when the
+    scales come off; all relative to |x_i||x_j| (Cauchy-Schwarz)."""
+    nrm = np.sqrt((X.astype(np.float64) ** 2).sum(1))
+    return (2.0 ** -22 + 2.0 ** -23 + (3 * (d // 16 + 1) + 1) * 2.0 ** -24) * np.outer(nrm, nrm)
+
+
+CASES = [(1, 65), (127, 72), (128, 80), (129, 16), (257, 100), (300, 7), (385, 129)]
+
+
+@pytest.mark.parametrize("mode", ["packed", "resident"])
+@pytest.mark.parametrize("n,d", CASES)
+def test_linear_within_the_split_bound(n, d, mode):
+    _torch_cuda()
+    X = _points(n, d, 100 + n)
+    with Engine(X, "linear", mode=mode) as eng:
+        K, diag = eng.K_rows(), eng.diag()
+    ref = X.astype(np.float64) @ X.astype(np.float64).T
+    assert np.all(np.abs(K - ref) <= _bound(X, d)), float(np.max(np.abs(K - ref) / np.maximum(_bound(X, d), 1e-300)))
+    assert np.array_equal(K, K.T) and np.array_equal(diag, np.diag(K))
+
+
+@pytest.mark.parametrize("mode,storage,n", [("packed", "f32", 8200), ("resident", "f32", 8200), ("packed", "f32", 8449),
+                                            ("packed", "f16", 8321), ("resident", "f16", 8321)])
+def test_tall_tiles_match_fp64(mode, storage, n):
+    torch = _torch_cuda()
+    d, g = 67, 0.01
+    X = _points(n, d, 7, spread=False)
+    with Engine(X, "gauss", g, mode=mode, storage=storage) as eng:
+        out = torch.empty((n, n), device="cuda")
+        eng.kkm.kkm_copy_kernel_rows(eng.ctx, 0, n, out)
+        X64 = eng.X.double()
+        sq = (X64 * X64).sum(1)
+        ref = torch.exp(-g * (sq[:, None] + sq[None, :] - 2.0 * (X64 @ X64.T)).clamp(min=0.0))
+        err = (out.double() - ref).abs()
+        # entries are at most 1: the exponent's error is 2 gamma times the
+        # product's plus a few roundings of its terms (below 16 here), and
+        # exp2 is good to a few units in the last place
+        nrm = float(sq.max())
+        tol = 2 * g * (2.0 ** -22 + 2.0 ** -23 + 19 * 2.0 ** -24) * nrm + 64 * 2.0 ** -24
+        tol += 2.0 ** -12 if storage == "f16" else 0.0
+        assert float(err.max()) <= tol, (float(err.max()), tol)
+        assert torch.equal(out, out.T)
+
+
+@pytest.mark.parametrize("kind", ["linear", "gauss"])
+@pytest.mark.parametrize("value", [np.inf, 3e19])
+def test_a_norm_past_fp32_takes_the_fp32_build(kind, value):
+    """One point with an infinite coordinate, or a finite one whose square is
+    past fp32's range: the entries among the other points are as without it,
+    and those with it are what fp32 products give."""
+    _torch_cuda()
+    X = np.abs(_points(200, 70, 3, spread=False)) + np.float32(0.5)
+    Y = X.copy()
+    Y[17, 4] = value
+    with Engine(Y, kind, 0.01, mode="packed") as eng:
+        K = eng.K_rows()
+    keep = np.arange(200) != 17
+    K64 = X.astype(np.float64) @ X.astype(np.float64).T
+    if kind == "gauss":
+        sq = np.diag(K64)
+        K64 = np.exp(-0.01 * (sq[:, None] + sq[None, :] - 2 * K64))
+    np.testing.assert_allclose(K[np.ix_(keep, keep)], K64[np.ix_(keep, keep)], rtol=2e-5)
+    if kind == "linear":
+        row = Y[17].astype(np.float64) @ Y[keep].astype(np.float64).T
+        np.testing.assert_allclose(K[17, keep], row, rtol=1e-5)
+        assert np.isinf(K[17, 17])
+
+
+@pytest.mark.parametrize("mode", ["packed", "resident"])
+def test_without_room_for_the_split_points(mode):
+    """A budget of exactly what kkm_plan asks for has no room for the split
+    points: the build runs on the fp32 matrix cores, and iterating works."""
+    _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    X = _points(700, 90, 5)
+    _, need = kkm.kkm_plan(700, 90, 9, kkm.KKM_LINEAR, 1 << 40, kkm.MODES[mode])
+    ref = X.astype(np.float64) @ X.astype(np.float64).T
+    nrm = np.sqrt(np.diag(ref))
+    with Engine(X, "linear", mode=mode, mem_budget=need + 4096, k_hint=9) as eng:
+        K = eng.K_rows()
+        _, it, _ = eng.iterate(np.arange(700, dtype=np.int32) % 9, 9, 3)
+        assert eng.info()["bytes_total"] <= need + 4096 and it == 3
+    assert np.all(np.abs(K - ref) <= 90 * 2.0 ** -24 * np.outer(nrm, nrm))
+
+
+def test_the_split_points_give_way_to_scratch():
+    """The split points fit beside the build but not beside the scratch of a
+    larger k: the scratch takes their room, and a rebuild gives the same K."""
+    _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    n, d = 1500, 784
+    X = _points(n, d, 6, spread=False)
+    _, need1 = kkm.kkm_plan(n, d, 1, kkm.KKM_LINEAR, 1 << 40, kkm.KKM_MODE_PACKED)
+    _, need = kkm.kkm_plan(n, d, 60, kkm.KKM_LINEAR, 1 << 40, kkm.KKM_MODE_PACKED)
+    split = (n + 256) * (d + 4) * 4
+    budget = max(need, need1 + split) + (1 << 16)
+    assert budget < need + split
+    with Engine(X, "linear", mode="packed", mem_budget=budget) as eng:
+        K = eng.K_rows()
+        cl = (np.arange(n) % 60).astype(np.int32)
+        held = eng.info()["bytes_total"]
+        _, it, _ = eng.iterate(cl, 60, 2)
+        assert it == 2 and eng.info()["bytes_total"] <= budget and held <= budget
+        P = kkm.make_params(mode=kkm.KKM_MODE_PACKED)
+        kkm.kkm_build_kernel(eng.ctx, eng.X, n, d, kkm.KKM_LINEAR, P)
+        np.testing.assert_allclose(eng.K_rows(), K, rtol=0, atol=float(_bound(X, d).max()) * 2)
