@@ -1,8 +1,9 @@
 // K = kappa(X X^T) with the product on the binary16 matrix cores (split_mma.h):
-// the K build wherever the split points are held (kkm_capi.cpp), all storages,
-// panels and blocks.  gemm_kappa.hip keeps the build on the fp32 matrix cores,
-// for points with a norm past fp32's range and for memory budgets without room
-// for the split points.
+// the K build from kSplitMinDpad coordinates up wherever the split points are
+// held (kkm_capi.cpp), all storages, panels and blocks.  gemm_kappa.hip keeps
+// the build on the fp32 matrix cores, for fewer coordinates, for points with a
+// norm past fp32's range and for memory budgets without room for the split
+// points.
 //
 // Tiles, layouts and epilogue are those of gemm_kappa.hip: the upper block
 // triangle of 128 x 128 tiles (I <= J), an entry's accumulator register and
@@ -22,9 +23,8 @@ namespace {
 typedef __attribute__((address_space(1))) const void gvoid;
 typedef __attribute__((address_space(3))) void lvoid;
 
-// Row bands of the square layouts: kBand workgroup rows (256 rows each) by all
-// their columns, columns outermost, so that the ~64 workgroups an XCD runs at
-// once cover 8 row pairs x 8 columns and their chunks meet in its L2.
+// Height of a band of tiles (Bands): the ~100 workgroups an XCD runs at once
+// cover a band's rows by a dozen columns, and their chunks meet in its L2.
 constexpr int kBand = 8;
 
 // kappa from acc = s_i s_j x_i . x_j: si = 1/s_i; cj = 1/s_j times -2c
@@ -66,8 +66,8 @@ struct BuildOut {
 // of the 32 x 32 block (bi, bj)) for recomputation: the square layouts each
 // pair once (i < j), a panel every entry it stores off the diagonal.  A scan of
 // the lanes' counts and one atomic per wavefront give the slots.
-template <typename KT, bool PANEL, int BI>
-__device__ inline void list_fixups(unsigned (&mk)[BI], int64_t gi0, int64_t gj0, bool inside, const BuildOut<KT>& o) {
+template <typename KT, bool PANEL>
+__device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, bool inside, const BuildOut<KT>& o) {
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int seg = (int)(blockIdx.x % kFixSegs);
   auto entry = [&](int bi, int bit, int64_t& gi, int64_t& gj) {
@@ -77,7 +77,7 @@ __device__ inline void list_fixups(unsigned (&mk)[BI], int64_t gi0, int64_t gj0,
   };
   unsigned cnt = 0;
 #pragma unroll
-  for (int bi = 0; bi < BI; ++bi) {
+  for (int bi = 0; bi < 2; ++bi) {
     if (!inside)  // a diagonal or last tile: drop what is not listed
       for (unsigned m = mk[bi]; m; m &= m - 1u) {
         int64_t gi, gj;
@@ -97,7 +97,7 @@ __device__ inline void list_fixups(unsigned (&mk)[BI], int64_t gi0, int64_t gj0,
   if (lane == 0 && total) base = atomicAdd(o.fix_count + seg, (unsigned long long)total);
   base = __shfl(base, 0, 64) + (pre - cnt);
 #pragma unroll
-  for (int bi = 0; bi < BI; ++bi)
+  for (int bi = 0; bi < 2; ++bi)
     for (unsigned m = mk[bi]; m; m &= m - 1u) {
       int64_t gi, gj;
       entry(bi, __ffs(m) - 1, gi, gj);
@@ -107,27 +107,26 @@ __device__ inline void list_fixups(unsigned (&mk)[BI], int64_t gi0, int64_t gj0,
     }
 }
 
-// One wavefront's part of tile (I, J): rows gi0 .. gi0 + 32 BI - 1 (inside row
-// tile I), columns gj0 .. gj0 + 63.  rinv, rcn: the rows' 1/s and (Gaussian)
+// One wavefront's part of tile (I, J): rows gi0 .. gi0 + 63, columns gj0 .. gj0 + 63.  rinv, rcn: the rows' 1/s and (Gaussian)
 // c|x|^2, in LDS; cf, cnj: the columns' factor (col_factor) and c|x|^2.  est:
 // Gaussian entries of the tile may need the fix-up.  Tw: 32 x 65 floats of LDS
 // of the wavefront's own (mirror tiles and binary16 storage), ordered within
 // the wavefront.
-template <int KIND, typename KT, bool PANEL, int BI>
-__device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv, const float* rcn,
+template <int KIND, typename KT, bool PANEL>
+__device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, const float* rcn,
                                       const float (&cf)[2], const float (&cnj)[2], int64_t I, int64_t J,
                                       int64_t gi0, int64_t gj0, bool est, float* Tw, const KappaParams& kp,
                                       const BuildOut<KT>& o) {
   constexpr bool kHalf = sizeof(KT) == 2;
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
-  unsigned mk[BI];  // the lane's entries whose estimate calls for the fix-up
+  unsigned mk[2];  // the lane's entries whose estimate calls for the fix-up
   // (the two versions' common loads and sums are kept from being merged ahead
   // of the branch, where they would hold a register per entry)
   auto kpass = [&](auto e_) {
     if constexpr (e_) asm volatile("; with the estimate" ::: "memory");
     else asm volatile("; without" ::: "memory");
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi) {
+    for (int bi = 0; bi < 2; ++bi) {
       // u = c|x_i|^2 + c|x_j|^2 rounds the same for (i, j) and (j, i) only
       // if the products are not fused into the sum
 #pragma clang fp contract(off)
@@ -156,10 +155,10 @@ __device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv,
   if (KIND == GAUSS && est) {
     unsigned any = 0u;
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi) any |= mk[bi];
+    for (int bi = 0; bi < 2; ++bi) any |= mk[bi];
     if (__ballot(any != 0u))
-      list_fixups<KT, PANEL, BI>(mk, gi0, gj0,
-                                 I != J && (PANEL ? gi0 + 32 * BI <= o.r1 && gj0 + 64 <= o.c1 : gj0 + 64 <= o.n), o);
+      list_fixups<KT, PANEL>(mk, gi0, gj0,
+                                 I != J && (PANEL ? gi0 + 64 <= o.r1 && gj0 + 64 <= o.c1 : gj0 + 64 <= o.n), o);
   }
 
   // The rows of tile (I, J) lie at a fixed stride S in every layout (packed:
@@ -185,7 +184,7 @@ __device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv,
     // a diagonal tile: diag K, and (square layouts) each pair from its entry
     // with i <= j, stored in both places
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
 #pragma unroll
@@ -207,7 +206,7 @@ __device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv,
         }
     return;
   }
-  const bool full = gi0 + 32 * BI <= rlim && gj0 + 64 <= clim;
+  const bool full = gi0 + 64 <= rlim && gj0 + 64 <= clim;
   if (!kHalf) {
     // fp32 goes straight from the matrix layout: each instruction writes rows
     // il and il + 4, 32 consecutive floats (128 bytes) each, at a uniform row
@@ -215,7 +214,7 @@ __device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv,
     const unsigned lane_b = ((unsigned)(4 * h) * (unsigned)S + (unsigned)l32) * 4u;
     char* const Kc = (char*)Kb;
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int iu = bi * 32 + 8 * (r >> 2) + (r & 3);
@@ -240,7 +239,7 @@ __device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv,
   if (kHalf) {
     // binary16 goes through the LDS tile, one row's 128 contiguous bytes per instruction
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi) {
+    for (int bi = 0; bi < 2; ++bi) {
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
@@ -259,59 +258,56 @@ __device__ inline void build_epilogue(floatx16 (&acc)[BI][2], const float* rinv,
   }
   if (!PANEL && !o.packed) {  // full storage: tile (J, I), rows j, columns i
 #pragma unroll
-    for (int bj = 0; bj < 2; ++bj)
+    for (int bj = 0; bj < 2; ++bj) {
 #pragma unroll
-      for (int b2 = 0; b2 < BI; b2 += 2) {
+      for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+        for (int r = 0; r < 16; ++r) Tw[l32 * 65 + bi * 32 + 8 * (r >> 2) + 4 * h + (r & 3)] = acc[bi][bj][r];
+      ordered();
+      const int64_t gi = gi0 + lane;  // I < J, so gi < n
+      const int64_t gj1 = gj0 + bj * 32;
+      const int nrows = (int)min<int64_t>(32, o.n - gj1);
+      KT* dst = o.K + gj1 * o.ld + gi;
+      auto put = [&](int rr) {
+        const float v = Tw[rr * 65 + lane];
+        __builtin_nontemporal_store((KT)(kHalf && o.kw ? v * (1.f / o.kw[gj1 + rr]) : v), dst + rr * o.ld);
+      };
+      if (nrows >= 32) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) Tw[l32 * 65 + bi * 32 + 8 * (r >> 2) + 4 * h + (r & 3)] = acc[b2 + bi][bj][r];
-        ordered();
-        const int64_t gi = gi0 + b2 * 32 + lane;  // I < J, so gi < n
-        const int64_t gj1 = gj0 + bj * 32;
-        const int nrows = (int)min<int64_t>(32, o.n - gj1);
-        KT* dst = o.K + gj1 * o.ld + gi;
-        auto put = [&](int rr) {
-          const float v = Tw[rr * 65 + lane];
-          __builtin_nontemporal_store((KT)(kHalf && o.kw ? v * (1.f / o.kw[gj1 + rr]) : v), dst + rr * o.ld);
-        };
-        if (nrows >= 32) {
-#pragma unroll
-          for (int rr = 0; rr < 32; ++rr) put(rr);
-        } else {
-          for (int rr = 0; rr < nrows; ++rr) put(rr);
-        }
-        ordered();
+        for (int rr = 0; rr < 32; ++rr) put(rr);
+      } else {
+        for (int rr = 0; rr < nrows; ++rr) put(rr);
       }
+      ordered();
+    }
   }
 }
 
-// The tiles of a launch: bands of kBand workgroup rows (rt row tiles each) by
-// their columns, column by column.  Square layouts: a band starts at the
-// column of its first row, and the few tiles left of a row's own first column
-// do nothing.
+// The tiles of a launch: bands of kBand row tiles by their columns, column by
+// column.  Square layouts: a band starts at the column of its first row, and
+// the few tiles left of a row's diagonal tile do nothing.
 struct Bands {
-  int64_t rows, cols, rt;  // workgroup rows, column tiles, row tiles per workgroup row
+  int64_t rows, cols;  // row and column tiles
   bool square;
   __host__ __device__ int64_t before(int64_t band) const {  // tiles in earlier bands
-    return kBand * (band * cols - (square ? kBand * rt * (band * (band - 1) / 2) : 0));
+    return kBand * (band * cols - (square ? kBand * (band * (band - 1) / 2) : 0));
   }
   __host__ __device__ int64_t nbands() const { return (rows + kBand - 1) / kBand; }
   __host__ __device__ int64_t height(int64_t band) const {
     const int64_t p = rows - band * kBand;
     return p < kBand ? p : kBand;
   }
-  __host__ __device__ int64_t first_col(int64_t band) const { return square ? band * kBand * rt : 0; }
+  __host__ __device__ int64_t first_col(int64_t band) const { return square ? band * kBand : 0; }
   __host__ __device__ int64_t total() const {
     const int64_t b = nbands() - 1;
     return before(b) + height(b) * (cols - first_col(b));
   }
-  // tile t: workgroup row m, column j
+  // tile t: row tile m, column tile j
   __device__ void tile(int64_t t, int64_t& m, int64_t& j) const {
     const int64_t last = nbands() - 1;
     int64_t band;
     if (square) {  // before(x) = t, for real x
-      const double a = 0.5 * (double)(kBand * kBand * rt), s = (double)(kBand * cols) + a;
+      const double a = 0.5 * (double)(kBand * kBand), s = (double)(kBand * cols) + a;
       const double disc = s * s - 4.0 * a * (double)t;
       band = (int64_t)((s - sqrt(disc > 0.0 ? disc : 0.0)) / (2.0 * a));
       band = min(max(band, (int64_t)0), last);
@@ -330,29 +326,29 @@ struct Bands {
 
 // Bound by the matrix cores (three binary16 products per fp32 one) at d of a
 // few hundred, by its stores below.  Measured on packed K against the fp32
-// matrix cores (gemm_kappa_kernel): n = 20000, d = 784 2.78 -> 1.03 ms; n =
-// 60000, d = 780 21.9 -> 8.5 ms (a product rate of 1.0 PFLOP/s); n = 50000, d
-// = 128 3.1 -> 1.85 ms; n = 5000, d = 300 91 -> 45 us; binary16 storage, n =
-// 40001, d = 301 4.3 -> 2.4 ms.  K's error against fp64 fell to 0.67-0.84 of
-// the fp32 build's on all of them (fewer roundings of the sum).
+// matrix cores (gemm_kappa.hip): n = 20000, d = 784 2.78 -> 0.98 ms; n = 60000,
+// d = 780 21.9 -> 8.5 ms (products at 1.0 PFLOP/s, where a library product of
+// binary16 matrices runs at 1.4); n = 50000, d = 128 3.1 -> 1.55 ms; n = 5000, d
+// = 300 91 -> 45 us; n = 120000, d = 54 9.0 -> 6.4 ms (4.5 TB/s of stores, which
+// alone run at 5.3); binary16 storage, n = 40001, d = 301 4.3 -> 1.9 ms.
 //
-// Workgroup: 64 BI rows x 128 columns, wavefront (wm, wn): 32 BI rows x 64
-// columns.  BI = 4 puts each wavefront in one row tile (wm picks it) and reads
-// 12 KB of operands from LDS per 24 matrix instructions; BI = 2 (a 128 x 128
-// tile) reads 8 KB per 12, which saturates LDS, but gives twice the workgroups
-// to small problems.  A chunk's units go from global memory straight to LDS,
-// double buffered: chunk c + 1 is requested once chunk c's operands are in
-// registers and arrives during its products; one barrier per chunk.
-template <int KIND, typename KT, bool PANEL, int BI>
-__global__ __launch_bounds__(256, 2) void gemm_split_kernel(
+// Workgroup: a 128 x 128 tile, wavefront (wm, wn) its 64 x 64 quarter.  A
+// chunk's units go from global memory straight to LDS, double buffered: chunk c
+// + 1 is requested once chunk c's operands are in registers and arrives during
+// its products; one barrier per chunk.  256 x 128 tiles (128 x 64 per
+// wavefront) need a quarter less LDS traffic per product but leave two
+// wavefronts per SIMD instead of three or four, and measured slower at every
+// width: n = 60000, d = 128 2.29 ms against 2.06, n = 40000, d = 784 3.71
+// against 3.63, n = 120000, d = 54 6.74 against 6.43.
+template <int KIND, typename KT, bool PANEL>
+__global__ __launch_bounds__(256, 3) void gemm_split_kernel(
     const half_t* __restrict__ Xf, const float* __restrict__ xinv, const float* __restrict__ nrm,
-    const unsigned* __restrict__ maxnrm_bits, const float* __restrict__ bmax, int64_t n_pad, int nch, Bands bands,
+    const unsigned* __restrict__ maxnrm_bits, const float* __restrict__ bmax, int nch, Bands bands,
     int64_t T, KappaParams kp, BuildOut<KT> o) {
-  constexpr int kA = 2 * BI, kUnits = 2 * (kA + 4), kPer = kUnits / 4;  // row blocks; units per chunk and wavefront
-  constexpr int kRows = 64 * BI;
+  constexpr int kUnits = 16, kPer = kUnits / 4;  // units per chunk: 4 row and 4 column blocks, hi and lo; per wavefront
   constexpr int kStageBytes = kUnits * 1024, kTBytes = 4 * 32 * 65 * 4;
   __shared__ __attribute__((aligned(1024))) char lds[2 * kStageBytes > kTBytes ? 2 * kStageBytes : kTBytes];
-  __shared__ __attribute__((aligned(16))) float rinv[kRows], rcn[kRows];
+  __shared__ __attribute__((aligned(16))) float rinv[kTile], rcn[kTile];
   const float maxnrm = __uint_as_float(*maxnrm_bits);
   if (!(maxnrm < INFINITY)) return;  // gemm_kappa_kernel builds K then (uniform)
 
@@ -360,26 +356,24 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(
   const int64_t b = blockIdx.x;
   const int64_t per = T >> 3, rem = T & 7, x = b & 7;
   const int64_t t = x * per + (x < rem ? x : rem) + (b >> 3);
-  constexpr int kRt = BI / 2;
-  int64_t I0, J;
-  bands.tile(t, I0, J);
-  I0 *= kRt;
+  int64_t I, J;
+  bands.tile(t, I, J);
   if (PANEL) {
-    I0 += o.r0 / kTile;
+    I += o.r0 / kTile;
     J += o.c0 / kTile;
-  } else if (J < I0) {
+  } else if (J < I) {
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31;
-  const int64_t row0 = I0 * kTile, col0 = J * kTile;
+  const int64_t row0 = I * kTile, col0 = J * kTile;
 
   // this wavefront's units of a chunk: unit u is part u % 2 of row block u / 2, then of the column blocks
   const half_t* src[kPer];
 #pragma unroll
   for (int v = 0; v < kPer; ++v) {
     const int u = wave * kPer + v, blk = u >> 1;
-    const int64_t gb = blk < kA ? row0 / 32 + blk : col0 / 32 + (blk - kA);
+    const int64_t gb = blk < 4 ? row0 / 32 + blk : col0 / 32 + (blk - 4);
     src[v] = Xf + split_unit(gb, nch, 0, u & 1) * kUnit + lane * 8;
   }
   auto fetch = [&](int c) {
@@ -389,22 +383,21 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(
       __builtin_amdgcn_global_load_lds((gvoid*)(src[v] + (int64_t)c * (2 * kUnit)), (lvoid*)(dst + v * 1024), 16, 0, 0);
   };
   fetch(0);
-  // the rows' and columns' factors (rows past n_pad are never stored)
-  for (int r = tid; r < kRows; r += 256) {
-    rinv[r] = xinv[row0 + r];
-    rcn[r] = KIND == GAUSS ? kp.neg_g_log2e * nrm[min(row0 + r, n_pad - 1)] : 0.f;
+  if (tid < kTile) {  // the rows' and columns' factors
+    rinv[tid] = xinv[row0 + tid];
+    rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm[row0 + tid] : 0.f;
   }
   float cf[2], cnj[2] = {0.f, 0.f};
 #pragma unroll
   for (int bj = 0; bj < 2; ++bj) {
     const int64_t j = col0 + wn * 64 + bj * 32 + l32;
     cf[bj] = col_factor<KIND>(xinv[j], kp);
-    if (KIND == GAUSS) cnj[bj] = kp.neg_g_log2e * nrm[min(j, n_pad - 1)];
+    if (KIND == GAUSS) cnj[bj] = kp.neg_g_log2e * nrm[j];
   }
 
-  floatx16 acc[BI][2];
+  floatx16 acc[2][2];
 #pragma unroll
-  for (int bi = 0; bi < BI; ++bi)
+  for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
@@ -416,28 +409,27 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
     const char* st = lds + (c & 1) * kStageBytes + lane * 16;
-    half8 a[BI][2], bb[2][2];
+    half8 a[2][2], bb[2][2];
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) a[bi][p] = *(const half8*)(st + ((wm * BI + bi) * 2 + p) * 1024);
+      for (int p = 0; p < 2; ++p) a[bi][p] = *(const half8*)(st + ((wm * 2 + bi) * 2 + p) * 1024);
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) bb[bj][p] = *(const half8*)(st + ((kA + wn * 2 + bj) * 2 + p) * 1024);
+      for (int p = 0; p < 2; ++p) bb[bj][p] = *(const half8*)(st + ((4 + wn * 2 + bj) * 2 + p) * 1024);
     __builtin_amdgcn_sched_barrier(0);
     if (c + 1 < nch) fetch(c + 1);
     __builtin_amdgcn_sched_barrier(0);
-    split_mfma<BI, 2>(a, bb, acc);
+    split_mfma(a, bb, acc);
   }
   __syncthreads();  // the stage buffers become the wavefronts' LDS tiles
 
-  const int64_t I = BI == 4 ? I0 + wm : I0;
-  const int64_t gi0 = row0 + wm * (32 * BI), gj0 = col0 + wn * 64;
+  const int64_t gi0 = row0 + wm * 64, gj0 = col0 + wn * 64;
   if (gi0 >= (PANEL ? o.r1 : o.n) || (!PANEL && gi0 > gj0 + 63)) return;  // nothing stored
   const bool est = KIND == GAUSS && (bmax ? gauss_needs_fix(1.f, bmax[I], bmax[J], kp)
                                           : gauss_needs_fix(1.f, maxnrm, maxnrm, kp));
-  build_epilogue<KIND, KT, PANEL, BI>(acc, rinv + wm * (32 * BI), rcn + wm * (32 * BI), cf, cnj, I, J, gi0, gj0, est,
+  build_epilogue<KIND, KT, PANEL>(acc, rinv + wm * 64, rcn + wm * 64, cf, cnj, I, J, gi0, gj0, est,
                                       (float*)lds + wave * (32 * 65), kp, o);
 }
 
@@ -445,30 +437,22 @@ namespace {
 
 template <int KIND, typename KT, bool PANEL>
 void launch_kind(const SplitPoints& sp, const float* nrm, const unsigned* maxnrm_bits, const float* bmax,
-                 int64_t n_pad, int64_t rows, int64_t cols, const KappaParams& kp, const BuildOut<KT>& o,
+                 int64_t rows, int64_t cols, const KappaParams& kp, const BuildOut<KT>& o,
                  hipStream_t s) {
-  // 256 x 128 tiles once they give every CU a few workgroups
-  const bool tall = rows * cols >= (PANEL ? kSplitTallTiles : 2 * kSplitTallTiles);
-  const int64_t rt = tall ? 2 : 1;
-  const Bands bands{(rows + rt - 1) / rt, cols, rt, !PANEL};
+  const Bands bands{rows, cols, !PANEL};
   const int64_t T = bands.total();
-  const dim3 grid((unsigned)T), block(256);
-  if (tall)
-    hipLaunchKernelGGL((gemm_split_kernel<KIND, KT, PANEL, 4>), grid, block, 0, s, sp.Xf, sp.xinv, nrm, maxnrm_bits,
-                       bmax, n_pad, sp.nch, bands, T, kp, o);
-  else
-    hipLaunchKernelGGL((gemm_split_kernel<KIND, KT, PANEL, 2>), grid, block, 0, s, sp.Xf, sp.xinv, nrm, maxnrm_bits,
-                       bmax, n_pad, sp.nch, bands, T, kp, o);
+  hipLaunchKernelGGL((gemm_split_kernel<KIND, KT, PANEL>), dim3((unsigned)T), dim3(256), 0, s, sp.Xf, sp.xinv, nrm,
+                     maxnrm_bits, bmax, sp.nch, bands, T, kp, o);
 }
 
 template <typename KT, bool PANEL>
 hipError_t launch_typed(const SplitPoints& sp, const float* nrm, const unsigned* maxnrm_bits, const float* bmax,
-                        int64_t n_pad, int64_t rows, int64_t cols, const KappaParams& kp, const BuildOut<KT>& o,
+                        int64_t rows, int64_t cols, const KappaParams& kp, const BuildOut<KT>& o,
                         hipStream_t s) {
   switch (kp.kind) {
-    case LINEAR: launch_kind<LINEAR, KT, PANEL>(sp, nrm, maxnrm_bits, bmax, n_pad, rows, cols, kp, o, s); break;
-    case POLY: launch_kind<POLY, KT, PANEL>(sp, nrm, maxnrm_bits, bmax, n_pad, rows, cols, kp, o, s); break;
-    default: launch_kind<GAUSS, KT, PANEL>(sp, nrm, maxnrm_bits, bmax, n_pad, rows, cols, kp, o, s); break;
+    case LINEAR: launch_kind<LINEAR, KT, PANEL>(sp, nrm, maxnrm_bits, bmax, rows, cols, kp, o, s); break;
+    case POLY: launch_kind<POLY, KT, PANEL>(sp, nrm, maxnrm_bits, bmax, rows, cols, kp, o, s); break;
+    default: launch_kind<GAUSS, KT, PANEL>(sp, nrm, maxnrm_bits, bmax, rows, cols, kp, o, s); break;
   }
   return hipGetLastError();
 }
@@ -481,13 +465,13 @@ hipError_t launch_gemm_split(const SplitPoints& sp, const float* nrm, const unsi
                              const float* bmax, hipStream_t s) {
   if (ld >= kMaxKStride) return hipErrorInvalidValue;
   const int64_t nt = (n + kTile - 1) / kTile;
-  if (sp.rows < (nt + 1) * kTile) return hipErrorInvalidValue;
+  if (sp.rows < nt * kTile) return hipErrorInvalidValue;
   if (f16) {
     const BuildOut<half_t> o{(half_t*)K, kw, diagK, fix_list, fix_count, seg_cap, n, ld, packed, 0, n, 0, n};
-    return launch_typed<half_t, false>(sp, nrm, maxnrm_bits, bmax, nt * kTile, nt, nt, kp, o, s);
+    return launch_typed<half_t, false>(sp, nrm, maxnrm_bits, bmax, nt, nt, kp, o, s);
   }
   const BuildOut<float> o{(float*)K, kw, diagK, fix_list, fix_count, seg_cap, n, ld, packed, 0, n, 0, n};
-  return launch_typed<float, false>(sp, nrm, maxnrm_bits, bmax, nt * kTile, nt, nt, kp, o, s);
+  return launch_typed<float, false>(sp, nrm, maxnrm_bits, bmax, nt, nt, kp, o, s);
 }
 
 hipError_t launch_gemm_split_panel(const SplitPoints& sp, const float* nrm, const unsigned* maxnrm_bits, int64_t n,
@@ -498,10 +482,9 @@ hipError_t launch_gemm_split_panel(const SplitPoints& sp, const float* nrm, cons
       ld >= kMaxKStride)
     return hipErrorInvalidValue;
   const int64_t nt = (n + kTile - 1) / kTile, rows = (r1 - r0 + kTile - 1) / kTile, cols = ld / kTile;
-  // the last workgroup row may reach one tile past the last row tile, the columns end inside n_pad
-  if (sp.rows < (nt + 1) * kTile || c0 / kTile + cols > nt) return hipErrorInvalidValue;
+  if (sp.rows < nt * kTile || c0 / kTile + cols > nt) return hipErrorInvalidValue;
   const BuildOut<float> o{K, nullptr, diagK, fix_list, fix_count, seg_cap, n, ld, 0, r0, r1, c0, c1};
-  return launch_typed<float, true>(sp, nrm, maxnrm_bits, nullptr, nt * kTile, rows, cols, kp, o, s);
+  return launch_typed<float, true>(sp, nrm, maxnrm_bits, nullptr, rows, cols, kp, o, s);
 }
 
 }  // namespace kkm

@@ -879,7 +879,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   }
   // The split points, where the budget holds them beside the iteration scratch.
   const bool f16 = storage == KKM_STORE_F16;
-  const bool splits = mode != KKM_MODE_ONTHEFLY && (panel || f16 || s.d_pad > kRegMaxDpad);
+  const bool splits = mode != KKM_MODE_ONTHEFLY && s.d_pad >= kSplitMinDpad;
   if (splits && !c->Xf) {
     const size_t bytes = split_bytes(s.n_pad, s.d_pad);
     const int32_t kh = std::min<int64_t>(params->k_hint, n);
@@ -889,13 +889,13 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
         c->split_allocs.push_back({p, bytes});
         c->held += bytes;
         c->Xf = (half_t*)p;
-        c->xinv = (float*)((char*)p + (bytes - (size_t)split_rows(s.n_pad) * 4));
+        c->xinv = (float*)((char*)p + (bytes - (size_t)s.n_pad * 4));
       } else {
         (void)hipGetLastError();
       }
     }
   }
-  const SplitPoints sp{c->Xf, c->xinv, split_rows(s.n_pad), (s.d_pad + 15) / 16};
+  const SplitPoints sp{c->Xf, c->xinv, s.n_pad, (s.d_pad + 15) / 16};
   if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, 1, c->stream); })))
     return rc;
   if ((rc = run(c, KKM_PHASE_STAGE, "stage", [&] {

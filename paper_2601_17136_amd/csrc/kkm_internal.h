@@ -24,6 +24,15 @@ constexpr int64_t kMaxKStride = (int64_t)1 << 23;
 constexpr int kStripe = 1024;
 constexpr int kChunk = 1024;
 
+// The product of the split points (split_mma.h) takes the place of fp32
+// matrix products from this d_pad up.  Its error against fp64 is that of two
+// roundings of each coordinate plus three roundings of the sum per 16
+// coordinates; the fp32 product's, one rounding per 2.  Measured over random
+// signs, image-like points and blobs, all kernels: 0.66-0.95 of the fp32
+// product's error at d = 32 .. 64 and less beyond, 0.91-1.03 at 24, 1.0-1.35
+// at 16 and 17, up to 1.8 at 6.
+constexpr int kSplitMinDpad = 32;
+
 // The sweep kernels of small widths take d_pad up to this.
 constexpr int kRegMaxDpad = 64;
 
@@ -60,9 +69,6 @@ inline int sym_seg_for(int64_t n, int k) {
   if (n <= kSymLargeN) return k <= 16 ? 16 : 32;
   return k <= 16 ? 16 : 64;
 }
-// Split build: 256 x 128 workgroup tiles from this many 128 x 128 tiles up
-// (counting both halves of a square layout's grid), 128 x 128 below.
-constexpr int64_t kSplitTallTiles = 2048;
 constexpr int kSymMaxK = 64;
 constexpr int kSymRedStripe = 256;  // columns per workgroup of the packed reduction
 
@@ -158,11 +164,7 @@ struct SplitPoints {
   int64_t rows;
   int nch;
 };
-// rows of the split points: a 256-row workgroup may reach one tile past n_pad
-inline int64_t split_rows(int64_t n_pad) { return n_pad + kTile; }
-inline size_t split_bytes(int64_t n_pad, int d_pad) {
-  return (size_t)split_rows(n_pad) * ((size_t)((d_pad + 15) / 16) * 64 + 4);
-}
+inline size_t split_bytes(int64_t rows, int d_pad) { return (size_t)rows * ((size_t)((d_pad + 15) / 16) * 64 + 4); }
 // launch_gemm_kappa and launch_gemm_kappa_panel from the split points; they
 // build nothing when the largest squared norm is not finite (those launch
 // beside them with only_inf set).

@@ -32,17 +32,16 @@ __host__ __device__ inline int64_t split_unit(int64_t blk, int nch, int c, int p
   return (blk * nch + c) * 2 + part;
 }
 
-// acc += A B^T of one chunk, for BI x BJ blocks of 32 x 32 (hi in part 0).
-template <int BI, int BJ>
-__device__ inline void split_mfma(const half8 (&a)[BI][2], const half8 (&b)[BJ][2], floatx16 (&acc)[BI][BJ]) {
-  // the three products of a block are BI * BJ instructions apart, so none
-  // waits for the one before it
+// acc += A B^T of one chunk, for 2 x 2 blocks of 32 x 32 (hi in part 0).
+__device__ inline void split_mfma(const half8 (&a)[2][2], const half8 (&b)[2][2], floatx16 (&acc)[2][2]) {
+  // a block's three products are four instructions apart, so none waits for
+  // the one before it
 #pragma unroll
   for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-      for (int bj = 0; bj < BJ; ++bj)
+      for (int bj = 0; bj < 2; ++bj)
         acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p == 2], b[bj][p == 1], acc[bi][bj], 0, 0, 0);
 }
 
