@@ -417,7 +417,8 @@ int kkm_block_assign(kkm_ctx *ctx, const float *E, int64_t a0, int64_t a1, int32
                      const int32_t *counts, int32_t *cl_out, int32_t *counts_out);
 
 /* Rows r0 .. r1-1 of K into out (device, (r1-r0) x n fp32 row-major).  In
- * ONTHEFLY mode the rows are computed by the same tile kernel the loop uses;
+ * ONTHEFLY mode the rows are computed from the staged points on the fp32
+ * matrix cores (the loop's sweep may round an entry's last bits otherwise);
  * in PACKED mode the part left of the stored triangle is read by symmetry.
  * Errors: KKM_ERR_ARG (range), KKM_ERR_STATE, KKM_ERR_HIP. */
 int kkm_copy_kernel_rows(kkm_ctx *ctx, int64_t r0, int64_t r1, float *out);

@@ -20,33 +20,9 @@ namespace kkm {
 
 namespace {
 
-typedef __attribute__((address_space(1))) const void gvoid;
-typedef __attribute__((address_space(3))) void lvoid;
-
 // Height of a band of tiles (Bands): the ~100 workgroups an XCD runs at once
 // cover a band's rows by a dozen columns, and their chunks meet in its L2.
 constexpr int kBand = 8;
-
-// kappa from acc = s_i s_j x_i . x_j: si = 1/s_i; cj = 1/s_j times -2c
-// (Gaussian, c = -gamma log2 e), gamma (polynomial) or 1 (linear), a product
-// with a power of two and so exact; u = c(|x_i|^2 + |x_j|^2).
-template <int KIND>
-__device__ inline float kappa_split(float acc, float si, float cj, float u, const KappaParams& kp) {
-  const float b = acc * si;
-  if (KIND == GAUSS) return __builtin_amdgcn_exp2f(fminf(fmaf(b, cj, u), 0.f));
-  if (KIND == LINEAR) return b * cj;
-  float t = fmaf(b, cj, kp.coef0), v = 1.f;
-  for (int e = kp.degree; e > 0; e >>= 1) {
-    if (e & 1) v *= t;
-    t *= t;
-  }
-  return v;
-}
-
-template <int KIND>
-__device__ inline float col_factor(float inv, const KappaParams& kp) {
-  return KIND == GAUSS ? inv * kp.m2c : KIND == POLY ? inv * kp.gamma : inv;
-}
 
 // What a build's epilogue writes and where.
 template <typename KT>
@@ -123,8 +99,8 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
   // (the two versions' common loads and sums are kept from being merged ahead
   // of the branch, where they would hold a register per entry)
   auto kpass = [&](auto e_) {
-    if constexpr (e_) asm volatile("; with the estimate" ::: "memory");
-    else asm volatile("; without" ::: "memory");
+    constexpr int P = decltype(e_)::value;
+    asm volatile("; version %0" ::"n"(P) : "memory");
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi) {
       // u = c|x_i|^2 + c|x_j|^2 rounds the same for (i, j) and (j, i) only
@@ -142,16 +118,15 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
 #pragma unroll
           for (int bj = 0; bj < 2; ++bj) {
             const float u = KIND == GAUSS ? cn[e] + cnj[bj] : 0.f;
-            const float v = kappa_split<KIND>(acc[bi][bj][4 * q + e], si[e], cf[bj], u, kp);
-            if (KIND == GAUSS && e_) mk[bi] = 2u * mk[bi] + (u * v < kp.fix_uthr ? 1u : 0u);
+            const float v = kappa_split<KIND, P == 2 ? 2 : 0>(acc[bi][bj][4 * q + e], si[e], cf[bj], u, kp);
+            if (P == 1) mk[bi] = 2u * mk[bi] + (u * v < kp.fix_uthr ? 1u : 0u);
             acc[bi][bj][4 * q + e] = v;
           }
         __builtin_amdgcn_sched_barrier(0);  // the rows' factors are not read further ahead (registers)
       }
     }
   };
-  if (KIND == GAUSS && est) kpass(std::true_type{});
-  else kpass(std::false_type{});
+  kappa_pass<KIND>(est, kp, kpass);
   if (KIND == GAUSS && est) {
     unsigned any = 0u;
 #pragma unroll
@@ -345,9 +320,8 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
     const half_t* __restrict__ Xf, const float* __restrict__ xinv, const float* __restrict__ nrm,
     const unsigned* __restrict__ maxnrm_bits, const float* __restrict__ bmax, int nch, Bands bands,
     int64_t T, KappaParams kp, BuildOut<KT> o) {
-  constexpr int kUnits = 16, kPer = kUnits / 4;  // units per chunk: 4 row and 4 column blocks, hi and lo; per wavefront
-  constexpr int kStageBytes = kUnits * 1024, kTBytes = 4 * 32 * 65 * 4;
-  __shared__ __attribute__((aligned(1024))) char lds[2 * kStageBytes > kTBytes ? 2 * kStageBytes : kTBytes];
+  constexpr int kTBytes = 4 * 32 * 65 * 4;
+  __shared__ __attribute__((aligned(1024))) char lds[kSplitLds > kTBytes ? kSplitLds : kTBytes];
   __shared__ __attribute__((aligned(16))) float rinv[kTile], rcn[kTile];
   const float maxnrm = __uint_as_float(*maxnrm_bits);
   if (!(maxnrm < INFINITY)) return;  // gemm_kappa_kernel builds K then (uniform)
@@ -368,21 +342,6 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31;
   const int64_t row0 = I * kTile, col0 = J * kTile;
 
-  // this wavefront's units of a chunk: unit u is part u % 2 of row block u / 2, then of the column blocks
-  const half_t* src[kPer];
-#pragma unroll
-  for (int v = 0; v < kPer; ++v) {
-    const int u = wave * kPer + v, blk = u >> 1;
-    const int64_t gb = blk < 4 ? row0 / 32 + blk : col0 / 32 + (blk - 4);
-    src[v] = Xf + split_unit(gb, nch, 0, u & 1) * kUnit + lane * 8;
-  }
-  auto fetch = [&](int c) {
-    char* dst = lds + (c & 1) * kStageBytes + wave * (kPer * 1024);
-#pragma unroll
-    for (int v = 0; v < kPer; ++v)
-      __builtin_amdgcn_global_load_lds((gvoid*)(src[v] + (int64_t)c * (2 * kUnit)), (lvoid*)(dst + v * 1024), 16, 0, 0);
-  };
-  fetch(0);
   if (tid < kTile) {  // the rows' and columns' factors
     rinv[tid] = xinv[row0 + tid];
     rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm[row0 + tid] : 0.f;
@@ -396,34 +355,7 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   }
 
   floatx16 acc[2][2];
-#pragma unroll
-  for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
-
-  for (int c = 0; c < nch; ++c) {
-    // chunk c has arrived (this wavefront's units; the barrier: everyone's),
-    // and everyone has read chunk c - 1, whose buffer chunk c + 1 takes
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-    __syncthreads();
-    const char* st = lds + (c & 1) * kStageBytes + lane * 16;
-    half8 a[2][2], bb[2][2];
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) a[bi][p] = *(const half8*)(st + ((wm * 2 + bi) * 2 + p) * 1024);
-#pragma unroll
-    for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) bb[bj][p] = *(const half8*)(st + ((4 + wn * 2 + bj) * 2 + p) * 1024);
-    __builtin_amdgcn_sched_barrier(0);
-    if (c + 1 < nch) fetch(c + 1);
-    __builtin_amdgcn_sched_barrier(0);
-    split_mfma(a, bb, acc);
-  }
-  __syncthreads();  // the stage buffers become the wavefronts' LDS tiles
+  split_tile(Xf, nch, row0 / 32, col0 / 32, lds, wave, lane, acc);  // ends with a barrier: the buffers become LDS tiles
 
   const int64_t gi0 = row0 + wm * 64, gj0 = col0 + wn * 64;
   if (gi0 >= (PANEL ? o.r1 : o.n) || (!PANEL && gi0 > gj0 + 63)) return;  // nothing stored

@@ -180,10 +180,12 @@ struct kkm_ctx {
   long long fix_cap = 0;                    // entries in all segments together
   int64_t fixups = 0;
   std::vector<Alloc> build_allocs;
-  // The split points (split_mma.h) the K build takes where memory allows, and
-  // gives back when something else needs the room; null: the fp32 build.
+  // The split points (split_mma.h) that the K build and, in sorted order, the
+  // on-the-fly sweep take where memory allows, given back when something else
+  // needs the room; null: the products run on the fp32 matrix cores.
   half_t* Xf = nullptr;
-  float* xinv = nullptr;
+  float* xinv = nullptr;    // row factors of the staged points
+  float* xinv_s = nullptr;  // on the fly: of the sorted points
   std::vector<Alloc> split_allocs;
 
   int k_ws = 0, iter_ws = 0;
@@ -249,13 +251,13 @@ void release(kkm_ctx* c, std::vector<Alloc>& owner) {
   owner.clear();
 }
 
-// The split points serve the K build only; later builds make them again.
+// Later builds make the split points again.
 void release_split(kkm_ctx* c) {
   if (!c->Xf) return;
   (void)hipStreamSynchronize(c->stream);
   release(c, c->split_allocs);
   c->Xf = nullptr;
-  c->xinv = nullptr;
+  c->xinv = c->xinv_s = nullptr;
 }
 
 int dalloc(kkm_ctx* c, void** p, size_t bytes, std::vector<Alloc>& owner, const char* what) {
@@ -592,13 +594,20 @@ int one_update(kkm_ctx* c, int t, const int* cur, int* nxt, float* z_out, float*
       return rc;
   } else {
     const Sizes& s = c->sz;
+    const bool split = c->Xf != nullptr;
     if ((rc = run(c, KKM_PHASE_OTHER, "gather_sorted", [&] {
+           if (split)
+             return launch_gather_split(c->Xp, c->nrm, c->xinv, c->maxnrm, b, cur, s.n_pad, s.d_pad, c->kp, c->Xf,
+                                        c->xinv_s, c->Xs, c->nrm_s, c->cs, c->stream);
            return launch_gather_sorted(c->Xp, c->nrm, b, cur, s.n_pad, s.d_pad, c->Xs, c->nrm_s, c->cs, c->stream);
          })))
       return rc;
     if ((rc = run(c, KKM_PHASE_ONTHEFLY, "onthefly", [&] {
-           return launch_onthefly(c->Xs, c->nrm_s, c->cs, c->maxnrm, b, s.d_pad, c->kp, c->otb, c->Epart,
-                                  c->Cpart, c->stream);
+           hipError_t e = launch_onthefly(c->Xs, c->nrm_s, c->cs, c->maxnrm, b, s.d_pad, c->kp, c->otb, c->Epart,
+                                          c->Cpart, split, c->stream);
+           if (e != hipSuccess || !split) return e;
+           return launch_onthefly_split(c->Xf, c->xinv_s, c->Xs, c->nrm_s, c->cs, c->maxnrm, b, s.d_pad, c->kp,
+                                        c->otb, c->Epart, c->Cpart, c->stream);
          })))
       return rc;
     if ((rc = run(c, KKM_PHASE_REDUCE, "onthefly_reduce", [&] {
@@ -879,9 +888,9 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   }
   // The split points, where the budget holds them beside the iteration scratch.
   const bool f16 = storage == KKM_STORE_F16;
-  const bool splits = mode != KKM_MODE_ONTHEFLY && s.d_pad >= kSplitMinDpad;
-  if (splits && !c->Xf) {
-    const size_t bytes = split_bytes(s.n_pad, s.d_pad);
+  const bool otf = mode == KKM_MODE_ONTHEFLY;
+  if (s.d_pad >= kSplitMinDpad && !c->Xf) {
+    const size_t split = split_bytes(s.n_pad, s.d_pad), bytes = split + (otf ? (size_t)s.n_pad * 4 : 0);
     const int32_t kh = std::min<int64_t>(params->k_hint, n);
     const size_t scratch = c->ws_allocs.empty() ? ws_bytes(c->wsz, kh > 0 ? kh : 1, mode) + 4096 : 0;
     if (c->held + bytes + scratch <= c->budget) {
@@ -889,7 +898,8 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
         c->split_allocs.push_back({p, bytes});
         c->held += bytes;
         c->Xf = (half_t*)p;
-        c->xinv = (float*)((char*)p + (bytes - (size_t)s.n_pad * 4));
+        c->xinv = (float*)((char*)p + (split - (size_t)s.n_pad * 4));
+        if (otf) c->xinv_s = c->xinv + s.n_pad;
       } else {
         (void)hipGetLastError();
       }
@@ -899,7 +909,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, 1, c->stream); })))
     return rc;
   if ((rc = run(c, KKM_PHASE_STAGE, "stage", [&] {
-         return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, c->Xf, c->xinv, sp.rows, c->stream);
+         return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, otf ? nullptr : c->Xf, c->xinv, c->stream);
        })))
     return rc;
   c->fixups = -1;  // read from the device on demand

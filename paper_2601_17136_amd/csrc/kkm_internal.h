@@ -154,9 +154,10 @@ struct IterBufs {
 };
 
 // ---------------------------------------------------------------- launchers
-// Xf (may be null): also the split points of n_split rows, see split_mma.h
+// xinv (may be null): also the split points' row factors; Xf (may be null):
+// also the split points (n_pad rows), see split_mma.h
 hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
-                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, int64_t n_split, hipStream_t s);
+                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, hipStream_t s);
 // The split points (split_mma.h): rows a multiple of 32, nch = ceil(d_pad / 16).
 struct SplitPoints {
   const half_t* Xf;
@@ -278,6 +279,8 @@ struct OtfTables {
   float* bmax;     // nt: largest squared norm of each sorted row block
 };
 int onthefly_segments(int64_t n);
+// Segment s of nseg covers column tiles [otf_seg_begin(s), otf_seg_begin(s + 1)).
+__device__ __host__ inline int otf_seg_begin(int s, int nt, int nseg) { return (int)((int64_t)s * nt / nseg); }
 int64_t onthefly_cpart_floats(int64_t n, int k);
 // partials per row-side and column-side entry of the sweep at this width
 // (2: one per wavefront half, for the register-operand kernel of small d)
@@ -290,7 +293,19 @@ hipError_t launch_diag_from_norms(const float* nrm, int64_t n, const KappaParams
 hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
                            const unsigned* maxnrm_bits, const IterBufs& b, int d_pad,
                            const KappaParams& kp, const OtfTables& tb, float* Epart, float* Cpart,
-                           hipStream_t s);
+                           bool only_inf, hipStream_t s);
+// The gather and the sweep from the split points, d_pad >= kSplitMinDpad: xinv
+// of the staged points, Xf and xinv_s in sorted order; Xs is written (and read)
+// only where an entry may need the fix-up or a norm is not finite.  The sweep
+// does nothing when the largest squared norm is not finite: launch_onthefly
+// runs beside it with only_inf set (and makes the tables: it goes first).
+hipError_t launch_gather_split(const float* Xp, const float* nrm, const float* xinv, const unsigned* maxnrm_bits,
+                               const IterBufs& b, const int* cl, int64_t n_pad, int d_pad, const KappaParams& kp,
+                               half_t* Xf, float* xinv_s, float* Xs, float* nrm_s, int* cs, hipStream_t s);
+hipError_t launch_onthefly_split(const half_t* Xf, const float* xinv_s, const float* Xs, const float* nrm_s,
+                                 const int* cs, const unsigned* maxnrm_bits, const IterBufs& b, int d_pad,
+                                 const KappaParams& kp, const OtfTables& tb, float* Epart, float* Cpart,
+                                 hipStream_t s);
 hipError_t launch_onthefly_reduce(const IterBufs& b, const float* Epart, const float* Cpart,
                                   const int* cs, const OtfTables& tb, int d_pad, hipStream_t s);
 hipError_t launch_kernel_rows(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,

@@ -157,9 +157,6 @@ __device__ inline void kappa_tile(floatx16 acc[2][2], const float* __restrict__ 
   }
 }
 
-// Segment bounds: segment s of nseg covers column tiles [seg_begin(s), seg_begin(s+1)).
-__device__ __host__ inline int seg_begin(int s, int nt, int nseg) { return (int)((int64_t)s * nt / nseg); }
-
 // bmax[P] = the largest squared norm among the sorted points of block P (128
 // threads per block; padding rows hold 0): an upper bound of |x_i|^2 + |x_j|^2
 // over a tile, with which the sweep skips the Gaussian fix-up estimate.
@@ -208,31 +205,39 @@ __global__ __launch_bounds__(1024) void onthefly_tables_kernel(const int* __rest
 }
 
 // FIX: the variant with the Gaussian fix-up path.  Both variants are
-// launched; each returns at once unless the largest norm calls for it.
+// launched; each returns at once unless the largest norm calls for it.  Beside
+// the split sweep (only_inf) only the FIX variant is, and it returns at once
+// unless the largest norm is not finite.
+template <int KIND, bool FIX>
+__device__ inline bool sweep_runs(const unsigned* maxnrm_bits, bool only_inf, const KappaParams& kp) {
+  if (only_inf) return !(__uint_as_float(*maxnrm_bits) < INFINITY);
+  return KIND != GAUSS || any_fix(maxnrm_bits, kp) == FIX;
+}
+
 template <int KIND, bool FIX>
 __global__ __launch_bounds__(256, 2) void onthefly_kernel(
     const float* __restrict__ Xs, const float* __restrict__ nrm_s, const int* __restrict__ cs,
     const unsigned* __restrict__ maxnrm_bits, const int* __restrict__ off,
     const int* __restrict__ cA, const int* __restrict__ nruns, const int64_t* __restrict__ cbase,
     int64_t n, int d_pad, int64_t ld, int nt, int nseg, int k, KappaParams kp,
-    float* __restrict__ Epart, float* __restrict__ Cpart) {
+    float* __restrict__ Epart, float* __restrict__ Cpart, bool only_inf) {
+  if (!sweep_runs<KIND, FIX>(maxnrm_bits, only_inf, kp)) return;
   // The block's row norms sit after the mainloop buffers in the same array,
   // so the compiler reloads them per tile instead of pinning 32 registers.
   __shared__ __attribute__((aligned(16))) float lds[kLdsFloats + kTile];
-  // Work items (segment s, row block I < seg_begin(s+1)), segment-major: the
+  // Work items (segment s, row block I < otf_seg_begin(s+1)), segment-major: the
   // hardware deals consecutive workgroups round-robin to the 8 XCDs, so every
   // XCD gets an even share, and the concurrent workgroups of one XCD sweep
   // the same column tiles (shared in its L2).
   int s = 0;
   int64_t first = 0;  // items before segment s
-  while (s + 1 < nseg && first + seg_begin(s + 1, nt, nseg) <= (int64_t)blockIdx.x) {
-    first += seg_begin(s + 1, nt, nseg);
+  while (s + 1 < nseg && first + otf_seg_begin(s + 1, nt, nseg) <= (int64_t)blockIdx.x) {
+    first += otf_seg_begin(s + 1, nt, nseg);
     ++s;
   }
   const int I = (int)((int64_t)blockIdx.x - first);
-  const int sb = seg_begin(s, nt, nseg), se = seg_begin(s + 1, nt, nseg);
+  const int sb = otf_seg_begin(s, nt, nseg), se = otf_seg_begin(s + 1, nt, nseg);
   if (I >= se) return;  // only past the last item
-  if (KIND == GAUSS && any_fix(maxnrm_bits, kp) != FIX) return;
   const int jt0 = sb > I ? sb : I, jt1 = se;
   const int64_t row0 = (int64_t)I * kTile;
 
@@ -448,21 +453,21 @@ __global__ __launch_bounds__(256, 2) void onthefly_reg_kernel(
     const unsigned* __restrict__ maxnrm_bits, const int* __restrict__ off,
     const int* __restrict__ cA, const int* __restrict__ nruns, const int64_t* __restrict__ cbase,
     const float* __restrict__ bmax, int64_t n, int64_t ld, int nt, int nseg, int k, KappaParams kp,
-    float* __restrict__ Epart, float* __restrict__ Cpart) {
+    float* __restrict__ Epart, float* __restrict__ Cpart, bool only_inf) {
+  if (!sweep_runs<KIND, FIX>(maxnrm_bits, only_inf, kp)) return;
   constexpr int d_pad = 2 * HP, ldsA = 2 * HP + 4;
   __shared__ __attribute__((aligned(16))) float rn[kTile];
   __shared__ __attribute__((aligned(16))) float As[kTile * ldsA];
   // work items as in onthefly_kernel: (segment s, row block I), segment-major
   int s = 0;
   int64_t first = 0;
-  while (s + 1 < nseg && first + seg_begin(s + 1, nt, nseg) <= (int64_t)blockIdx.x) {
-    first += seg_begin(s + 1, nt, nseg);
+  while (s + 1 < nseg && first + otf_seg_begin(s + 1, nt, nseg) <= (int64_t)blockIdx.x) {
+    first += otf_seg_begin(s + 1, nt, nseg);
     ++s;
   }
   const int I = (int)((int64_t)blockIdx.x - first);
-  const int sb = seg_begin(s, nt, nseg), se = seg_begin(s + 1, nt, nseg);
+  const int sb = otf_seg_begin(s, nt, nseg), se = otf_seg_begin(s + 1, nt, nseg);
   if (I >= se) return;
-  if (KIND == GAUSS && any_fix(maxnrm_bits, kp) != FIX) return;
   const int jt0 = sb > I ? sb : I, jt1 = se;
   const int64_t row0 = (int64_t)I * kTile;
 
@@ -635,7 +640,7 @@ __global__ __launch_bounds__(256) void onthefly_reduce_kernel(
     const int Q = (int)(col / kTile);
     f4 e = {0.f, 0.f, 0.f, 0.f};
     for (int s = 0; s < nseg; ++s) {
-      const int sb = seg_begin(s, nt, nseg), se = seg_begin(s + 1, nt, nseg);
+      const int sb = otf_seg_begin(s, nt, nseg), se = otf_seg_begin(s + 1, nt, nseg);
       if (se <= Q) continue;
       const int64_t c0 = (int64_t)(sb > Q ? sb : Q) * kTile;
       const int64_t c1 = (int64_t)se * kTile < b.n ? (int64_t)se * kTile : b.n;
@@ -729,25 +734,27 @@ int64_t onthefly_cpart_floats(int64_t n, int k) {
 hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
                            const unsigned* maxnrm_bits, const IterBufs& b, int d_pad,
                            const KappaParams& kp, const OtfTables& tb, float* Epart, float* Cpart,
-                           hipStream_t s) {
+                           bool only_inf, hipStream_t s) {
   const int nt = (int)((b.n + kTile - 1) / kTile), nseg = onthefly_segments(b.n);
   hipLaunchKernelGGL(onthefly_tables_kernel, dim3(1), dim3(1024), 0, s, cs, b.n, nt, tb.cA,
                      tb.nruns, tb.cbase);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   int64_t items = 0;  // (segment, row block) pairs right of the diagonal
-  for (int q = 0; q < nseg; ++q) items += seg_begin(q + 1, nt, nseg);
+  for (int q = 0; q < nseg; ++q) items += otf_seg_begin(q + 1, nt, nseg);
   dim3 grid((unsigned)items), block(256);
-  if (d_pad <= kRegMaxDpad) {
+  if (d_pad <= kRegMaxDpad || only_inf) {  // (the split sweep reads the block maxima at every width)
     if (d_pad % 8) return hipErrorInvalidValue;
     if (kp.kind == GAUSS) {
       hipLaunchKernelGGL(blockmax_kernel, dim3((unsigned)nt), dim3(kTile), 0, s, nrm_s, tb.bmax);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
+  }
+  if (d_pad <= kRegMaxDpad) {
 #define KKM_OTF_REG(KIND, FIX, HP)                                                                          \
   hipLaunchKernelGGL((onthefly_reg_kernel<KIND, FIX, HP>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits, b.off, \
-                     tb.cA, tb.nruns, tb.cbase, tb.bmax, b.n, b.ld, nt, nseg, b.k, kp, Epart, Cpart)
+                     tb.cA, tb.nruns, tb.cbase, tb.bmax, b.n, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf)
 #define KKM_OTF_REG_HP(KIND, FIX)           \
   switch (d_pad / 2) {                      \
     case 4: KKM_OTF_REG(KIND, FIX, 4); break;   \
@@ -764,7 +771,7 @@ hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
     } else if (kp.kind == POLY) {
       KKM_OTF_REG_HP(POLY, false);
     } else {
-      KKM_OTF_REG_HP(GAUSS, false);
+      if (!only_inf) KKM_OTF_REG_HP(GAUSS, false);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
       KKM_OTF_REG_HP(GAUSS, true);
@@ -775,17 +782,18 @@ hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
   }
   if (kp.kind == LINEAR) {
     hipLaunchKernelGGL((onthefly_kernel<LINEAR, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
   } else if (kp.kind == POLY) {
     hipLaunchKernelGGL((onthefly_kernel<POLY, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
   } else {
-    hipLaunchKernelGGL((onthefly_kernel<GAUSS, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart);
+    if (!only_inf)
+      hipLaunchKernelGGL((onthefly_kernel<GAUSS, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((onthefly_kernel<GAUSS, true>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
   }
   return hipGetLastError();
 }

@@ -21,6 +21,8 @@
 #pragma once
 #include "tile_mma.h"
 
+#include <type_traits>
+
 namespace kkm {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -30,6 +32,19 @@ constexpr int kUnit = 512;  // binary16 values in a unit
 // unit (block of 32 points, chunk of 16 coordinates, part): part 0 = hi, 1 = lo
 __host__ __device__ inline int64_t split_unit(int64_t blk, int nch, int c, int part) {
   return (blk * nch + c) * 2 + part;
+}
+
+// One lane's 8 coordinates v, scaled by sc, as hi at u and lo one unit further.
+__device__ inline void split_store(const float (&v)[8], float sc, half_t* u) {
+  half8 hi, lo;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float x = v[e] * sc;
+    hi[e] = (half_t)x;
+    lo[e] = (half_t)(x - (float)hi[e]);
+  }
+  *(half8*)u = hi;
+  *(half8*)(u + kUnit) = lo;
 }
 
 // acc += A B^T of one chunk, for 2 x 2 blocks of 32 x 32 (hi in part 0).
@@ -43,6 +58,97 @@ __device__ inline void split_mfma(const half8 (&a)[2][2], const half8 (&b)[2][2]
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj)
         acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p == 2], b[bj][p == 1], acc[bi][bj], 0, 0, 0);
+}
+
+typedef __attribute__((address_space(1))) const void gvoid;
+typedef __attribute__((address_space(3))) void lvoid;
+
+constexpr int kSplitLds = 2 * 16 * 1024;  // split_tile's LDS: two chunks of 16 units
+
+// The wavefront's 64 x 64 quarter (wm = wave / 2, wn = wave % 2) of the tile
+// whose 128 rows start at block rb and whose columns start at block cb of the
+// split points, laid out as mma_tile's.  256 threads.  A chunk's units (4 row
+// and 4 column blocks, hi and lo) go from global memory straight to LDS, double
+// buffered: chunk c + 1 is requested once chunk c's operands are in registers
+// and arrives during its products; one barrier per chunk and one at the end.
+__device__ inline void split_tile(const half_t* __restrict__ Xf, int nch, int64_t rb, int64_t cb, char* lds, int wave,
+                                  int lane, floatx16 (&acc)[2][2]) {
+  constexpr int kPer = 4;  // units per wavefront: unit u = 4 wave + v is part u % 2 of block u / 2
+  const int wm = wave >> 1, wn = wave & 1;
+  const half_t* src[kPer];
+#pragma unroll
+  for (int v = 0; v < kPer; ++v) {
+    const int u = wave * kPer + v, blk = u >> 1;
+    src[v] = Xf + split_unit(blk < 4 ? rb + blk : cb + (blk - 4), nch, 0, u & 1) * kUnit + lane * 8;
+  }
+  auto fetch = [&](int c) {
+    char* dst = lds + (c & 1) * (kSplitLds / 2) + wave * (kPer * 1024);
+#pragma unroll
+    for (int v = 0; v < kPer; ++v)
+      __builtin_amdgcn_global_load_lds((gvoid*)(src[v] + (int64_t)c * (2 * kUnit)), (lvoid*)(dst + v * 1024), 16, 0, 0);
+  };
+  fetch(0);
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
+  for (int c = 0; c < nch; ++c) {
+    // chunk c has arrived (this wavefront's units; the barrier: everyone's),
+    // and everyone has read chunk c - 1, whose buffer chunk c + 1 takes
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __syncthreads();
+    const char* st = lds + (c & 1) * (kSplitLds / 2) + lane * 16;
+    half8 a[2][2], b[2][2];
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) a[bi][p] = *(const half8*)(st + ((wm * 2 + bi) * 2 + p) * 1024);
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) b[bj][p] = *(const half8*)(st + ((4 + wn * 2 + bj) * 2 + p) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+    if (c + 1 < nch) fetch(c + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    split_mfma(a, b, acc);
+  }
+  __syncthreads();
+}
+
+// kappa from acc = s_i s_j x_i . x_j: si = 1/s_i; cj = 1/s_j times -2c
+// (Gaussian, c = -gamma log2 e), gamma (polynomial) or 1 (linear), a product
+// with a power of two and so exact; u = c(|x_i|^2 + |x_j|^2).
+// DEG: the polynomial's degree, or 0 for any (a loop per entry).
+template <int KIND, int DEG>
+__device__ inline float kappa_split(float acc, float si, float cj, float u, const KappaParams& kp) {
+  const float b = acc * si;
+  if (KIND == GAUSS) return __builtin_amdgcn_exp2f(fminf(fmaf(b, cj, u), 0.f));
+  if (KIND == LINEAR) return b * cj;
+  float t = fmaf(b, cj, kp.coef0), v = 1.f;
+  if (DEG == 2) return t * t;
+  for (int e = kp.degree; e > 0; e >>= 1) {
+    if (e & 1) v *= t;
+    t *= t;
+  }
+  return v;
+}
+
+// The pass over a tile's entries in its versions, the one that applies:
+// pass(integral_constant<P>) with P = 0 in general, 1 for the Gaussian with
+// the fix-up estimate, 2 for the polynomial of degree 2 (the paper's kernel:
+// the general loop costs a few scalar branches per entry).
+template <int KIND, typename F>
+__device__ inline void kappa_pass(bool est, const KappaParams& kp, F&& pass) {
+  if (KIND == GAUSS && est) pass(std::integral_constant<int, 1>{});
+  else if (KIND == POLY && kp.degree == 2) pass(std::integral_constant<int, 2>{});
+  else pass(std::integral_constant<int, 0>{});
+}
+
+template <int KIND>
+__device__ inline float col_factor(float inv, const KappaParams& kp) {
+  return KIND == GAUSS ? inv * kp.m2c : KIND == POLY ? inv * kp.gamma : inv;
 }
 
 }  // namespace kkm

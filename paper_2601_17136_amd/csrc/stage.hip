@@ -18,11 +18,11 @@ namespace kkm {
 // larger than what the word already holds.  A stale read only costs a
 // redundant atomic.
 //
-// Xf (may be null): the split points in operand order (split_mma.h), n_split
-// rows (a multiple of kStageBlk; rows past n are zero), and xinv[i] = 1 / s_i,
-// the power of two that undoes row i's scale.  The rows' largest coordinates
-// come from the same pass as the norms, and the second pass reads the staged
-// rows back from cache.
+// xinv (may be null): xinv[i] = 1 / s_i, the power of two that undoes row i's
+// scale in the split points (split_mma.h); Xf (may be null): those points in
+// operand order, zero past n.  The rows' largest coordinates come from the
+// same pass as the norms, and the second pass reads the staged rows back from
+// cache.
 constexpr int kStageRows = 4;
 constexpr int kStageWaves = 4;
 constexpr int kStageBlk = 32;
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
         mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], off, 64));
       }
       if (lane == r && i0 + r < n_pad) nrm[i0 + r] = s[r];
-      if (lane == r && Xf) {
+      if (lane == r && xinv) {
         // s_i = 2^(14 - e) for a largest coordinate in [2^e, 2^(e+1)), at most
         // 2^126; 1 for a zero row and for one that holds an infinity
         const int e = max((int)(__float_as_uint(mx[r]) >> 23), 1) - 127;
@@ -91,29 +91,19 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
   const float* row = Xp + (b0 + l) * d_pad + 8 * h;
   for (int c = w; c < nch; c += kStageWaves) {
     float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (b0 < n_pad && 16 * c + 8 * h < d_pad) {  // n_pad and d_pad are multiples of the block and of 8
+    if (16 * c + 8 * h < d_pad) {  // (a multiple of 8)
       const float4 x0 = *(const float4*)(row + 16 * c), x1 = *(const float4*)(row + 16 * c + 4);
       v[0] = x0.x, v[1] = x0.y, v[2] = x0.z, v[3] = x0.w;
       v[4] = x1.x, v[5] = x1.y, v[6] = x1.z, v[7] = x1.w;
     }
-    half8 hi, lo;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float x = v[e] * sc;
-      hi[e] = (half_t)x;
-      lo[e] = (half_t)(x - (float)hi[e]);
-    }
-    half_t* u = Xf + split_unit(blockIdx.x, nch, c, 0) * kUnit + lane * 8;
-    *(half8*)u = hi;
-    *(half8*)(u + kUnit) = lo;
+    split_store(v, sc, Xf + split_unit(blockIdx.x, nch, c, 0) * kUnit + lane * 8);
   }
 }
 
 hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
-                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, int64_t n_split, hipStream_t s) {
-  const int64_t rows = Xf ? n_split : n_pad;
-  if (rows % kStageBlk || n_pad % kStageBlk || rows < n_pad) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(rows / kStageBlk));
+                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, hipStream_t s) {
+  if (n_pad % kStageBlk || d_pad % 8 || (Xf && !xinv)) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(n_pad / kStageBlk));
   hipLaunchKernelGGL(stage_kernel, grid, dim3(64 * kStageWaves), 0, s, X, n, d, d_pad, n_pad, Xp, nrm,
                      maxnrm_bits, Xf, xinv);
   return hipGetLastError();

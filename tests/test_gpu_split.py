@@ -7,7 +7,7 @@ row tile more or less than the bands of eight its tiles are dealt in.
 import numpy as np
 import pytest
 
-from gpu_helpers import Engine
+from gpu_helpers import TOL, Engine, assignment_mismatches, rel_err, rowscaled_err
 
 pytestmark = pytest.mark.gpu
 
@@ -138,3 +138,66 @@ def test_the_split_points_give_way_to_scratch():
         P = kkm.make_params(mode=kkm.KKM_MODE_PACKED)
         kkm.kkm_build_kernel(eng.ctx, eng.X, n, d, kkm.KKM_LINEAR, P)
         np.testing.assert_allclose(eng.K_rows(), K, rtol=0, atol=float(_bound(X, d).max()) * 2)
+
+
+def _check_step(X, kind, g, c, p, cl, k, eng, oracle):
+    ref = oracle.step_full(oracle.Kernel(kind, g, c, p).matrix(X), cl, k)
+    out = eng.step(cl, k)
+    np.testing.assert_array_equal(out["counts"], ref["counts"])
+    assert rowscaled_err(out["E"], ref["E"]) <= 1e-5 and rowscaled_err(out["D"], ref["D"]) <= TOL
+    assert rel_err(out["z"], ref["z"]) <= 1e-5
+    assignment_mismatches(out["cl"], ref["cl"], ref["D"])
+    return out
+
+
+@pytest.mark.parametrize("kind", ["gauss", "poly", "linear"])
+@pytest.mark.parametrize("n,d,k", [(1, 32, 1), (127, 25, 3), (128, 33, 2), (129, 48, 9), (300, 56, 40), (640, 64, 5),
+                                   (257, 65, 3), (700, 100, 30), (385, 130, 7)])
+def test_on_the_fly_step(oracle, n, d, k, kind):
+    """Sweeps of two to four chunks held in LDS and of chunks staged per tile;
+    blocks of one cluster and of several, ragged last tiles."""
+    _torch_cuda()
+    X = _points(n, d, 40 + n, spread=False) + np.float32(0.25)
+    cl = np.random.default_rng(n).integers(0, k, n).astype(np.int32)
+    g, c, p = {"gauss": (1.0 / d, 0.0, 1), "poly": (1.0 / d, 1.0, 2 if d % 2 else 3), "linear": (1.0, 0.0, 1)}[kind]
+    with Engine(X, kind, g, c, p, mode="onthefly") as eng:
+        out = _check_step(X, kind, g, c, p, cl, k, eng, oracle)
+        again = eng.step(cl, k)
+        assert np.array_equal(out["E"], again["E"]) and out["J"] == again["J"]
+
+
+@pytest.mark.parametrize("d", [40, 90])
+def test_on_the_fly_fixups_and_small_budgets(oracle, d):
+    """Points far from the origin, so that Gaussian entries are recomputed from
+    the differences inside the sweep; once with the split points and once in
+    exactly the budget kkm_plan asks for, which has no room for them."""
+    _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    n, k = 500, 6
+    X = 0.3 * _points(n, d, 9, spread=False) + np.float32(20.0)
+    cl = np.random.default_rng(1).integers(0, k, n).astype(np.int32)
+    with Engine(X, "gauss", 0.05, mode="onthefly") as eng:
+        _check_step(X, "gauss", 0.05, 0.0, 1, cl, k, eng, oracle)
+    _, need = kkm.kkm_plan(n, d, k, kkm.KKM_GAUSS, 1 << 40, kkm.KKM_MODE_ONTHEFLY)
+    with Engine(X, "gauss", 0.05, mode="onthefly", mem_budget=need + 4096, k_hint=k) as eng:
+        _check_step(X, "gauss", 0.05, 0.0, 1, cl, k, eng, oracle)
+        assert eng.info()["bytes_total"] <= need + 4096
+
+
+@pytest.mark.parametrize("d", [40, 90])
+def test_on_the_fly_past_fp32_norms(d):
+    """A point whose squared norm is past fp32's range: the other clusters'
+    sums over the other points are finite and as without it."""
+    _torch_cuda()
+    X = np.abs(_points(300, d, 3, spread=False)) + np.float32(0.5)
+    X[17, 4] = 3e19
+    cl = (np.arange(300) % 3).astype(np.int32)
+    cl[17] = 2
+    with Engine(X, "linear", mode="onthefly") as eng:
+        E = eng.step(cl, 3)["E"]
+    X64 = X.astype(np.float64)
+    keep = np.arange(300) != 17
+    for j in (0, 1):
+        ref = X64[keep] @ X64[cl == j].sum(0)
+        np.testing.assert_allclose(E[keep, j], ref, rtol=1e-5)
+    assert np.isinf(E[17, 2])
