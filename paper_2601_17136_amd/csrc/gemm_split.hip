@@ -83,7 +83,7 @@ __device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, 
     }
 }
 
-// One wavefront's part of tile (I, J): rows gi0 .. gi0 + 63, columns gj0 .. gj0 + 63.  rinv, rcn: the rows' 1/s and (Gaussian)
+// One wavefront's part of tile (I, J): rows gi0 .. gi0 + 63, columns gj0 .. gj0 + 63.  rinv, rcn: the rows' -1/s and (Gaussian)
 // c|x|^2, in LDS; cf, cnj: the columns' factor (col_factor) and c|x|^2.  est:
 // Gaussian entries of the tile may need the fix-up.  Tw: 32 x 65 floats of LDS
 // of the wavefront's own (mirror tiles and binary16 storage), ordered within
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   const int64_t row0 = I * kTile, col0 = J * kTile;
 
   if (tid < kTile) {  // the rows' and columns' factors
-    rinv[tid] = xinv[row0 + tid];
+    rinv[tid] = -xinv[row0 + tid];  // the product comes negated
     rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm[row0 + tid] : 0.f;
   }
   float cf[2], cnj[2] = {0.f, 0.f};

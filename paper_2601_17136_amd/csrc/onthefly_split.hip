@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256, 2) void onthefly_split_kernel(
   const int nch = kNarrow ? NCH : (d_pad + 15) / 16;
   float* const cp = Cpart + cbase[I] * (kHalves * kTile);
   if (tid < kTile) {
-    rinv[tid] = xinv_s[row0 + tid];
+    rinv[tid] = -xinv_s[row0 + tid];  // the product comes negated
     rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm_s[row0 + tid] : 0.f;
   }
   if constexpr (kNarrow) {
@@ -247,7 +247,11 @@ __global__ __launch_bounds__(256, 2) void onthefly_split_kernel(
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-          for (int p = 0; p < 2; ++p) a[bi][p] = *(const half8*)(as + ((bi * NCH + c) * 2 + p) * 1024);
+          for (int p = 0; p < 2; ++p) {
+            a[bi][p] = *(const half8*)(as + ((bi * NCH + c) * 2 + p) * 1024);
+            if (c >= split_turn(NCH)) a[bi][p] = -a[bi][p];
+          }
+        if (c == split_turn(NCH)) split_negate(acc);
         split_mfma(a, b[c & 1], acc);
         __builtin_amdgcn_sched_barrier(0);  // operands are read one chunk ahead, not further (registers)
       }

@@ -34,6 +34,21 @@ __host__ __device__ inline int64_t split_unit(int64_t blk, int nch, int c, int p
   return (blk * nch + c) * 2 + part;
 }
 
+// The matrix instruction rounds its sum down (towards minus infinity; seen in
+// sums of either sign, about -2.7e-11 of the sum per coordinate of a positive
+// row), which the sums of K over a cluster, and the objective's differences of
+// them, would show.  So the last part of the chunks is added to the negated
+// sum, with the rows' operands negated: there the same rounding goes the other
+// way.  The sum of non-negative products grows with the chunks, and the two
+// parts' roundings cancel when the first has 1/sqrt(2) of them (for products
+// of random sign 0.63 would do).  The result is the negated product.
+__device__ inline int split_turn(int nch) { return (nch * 45 + 32) >> 6; }
+__device__ inline void split_negate(floatx16 (&acc)[2][2]) {
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = -acc[bi][bj];
+}
 // One lane's 8 coordinates v, scaled by sc, as hi at u and lo one unit further.
 __device__ inline void split_store(const float (&v)[8], float sc, half_t* u) {
   half8 hi, lo;
@@ -67,7 +82,7 @@ constexpr int kSplitLds = 2 * 16 * 1024;  // split_tile's LDS: two chunks of 16 
 
 // The wavefront's 64 x 64 quarter (wm = wave / 2, wn = wave % 2) of the tile
 // whose 128 rows start at block rb and whose columns start at block cb of the
-// split points, laid out as mma_tile's.  256 threads.  A chunk's units (4 row
+// split points, negated (split_turn), laid out as mma_tile's.  256 threads.  A chunk's units (4 row
 // and 4 column blocks, hi and lo) go from global memory straight to LDS, double
 // buffered: chunk c + 1 is requested once chunk c's operands are in registers
 // and arrives during its products; one barrier per chunk and one at the end.
@@ -94,7 +109,7 @@ __device__ inline void split_tile(const half_t* __restrict__ Xf, int nch, int64_
     for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
-  for (int c = 0; c < nch; ++c) {
+  auto step = [&](int c, auto negated) {
     // chunk c has arrived (this wavefront's units; the barrier: everyone's),
     // and everyone has read chunk c - 1, whose buffer chunk c + 1 takes
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -112,12 +127,23 @@ __device__ inline void split_tile(const half_t* __restrict__ Xf, int nch, int64_
     __builtin_amdgcn_sched_barrier(0);
     if (c + 1 < nch) fetch(c + 1);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (negated) {
+#pragma unroll
+      for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) a[bi][p] = -a[bi][p];
+    }
     split_mfma(a, b, acc);
-  }
+  };
+  const int turn = split_turn(nch);
+  int c = 0;
+  for (; c < turn; ++c) step(c, std::false_type{});
+  split_negate(acc);
+  for (; c < nch; ++c) step(c, std::true_type{});
   __syncthreads();
 }
 
-// kappa from acc = s_i s_j x_i . x_j: si = 1/s_i; cj = 1/s_j times -2c
+// kappa from acc = -s_i s_j x_i . x_j: si = -1/s_i; cj = 1/s_j times -2c
 // (Gaussian, c = -gamma log2 e), gamma (polynomial) or 1 (linear), a product
 // with a power of two and so exact; u = c(|x_i|^2 + |x_j|^2).
 // DEG: the polynomial's degree, or 0 for any (a loop per entry).
