@@ -201,12 +201,13 @@ struct kkm_ctx {
   double* obj = nullptr;
   std::vector<Alloc> hist_allocs;
 
-  // K-means++ seeding scratch (first use after a build): n floats kd, D,
-  // best, n ints bestc, per-block fp64 sums, KKM_MAX_K center indices
+  // K-means++ seeding scratch (first use after a build): n floats kd, two
+  // buffers of n floats D and of its per-block fp64 sums, n ints bestc,
+  // KKM_MAX_K center indices
   std::vector<Alloc> seed_allocs;
-  float *sd_kd = nullptr, *sd_D = nullptr, *sd_best = nullptr;
+  float *sd_kd = nullptr, *sd_D[2] = {nullptr, nullptr};
   int *sd_bestc = nullptr, *sd_centers = nullptr;
-  double* sd_bsum = nullptr;
+  double* sd_bsum[2] = {nullptr, nullptr};
 
   void* scratch = nullptr;  // this device's static scratch (kkm_iterate_noalloc)
 
@@ -342,9 +343,9 @@ void free_hist(kkm_ctx* c) {
 
 void free_seed(kkm_ctx* c) {
   release(c, c->seed_allocs);
-  c->sd_kd = c->sd_D = c->sd_best = nullptr;
+  c->sd_kd = c->sd_D[0] = c->sd_D[1] = nullptr;
   c->sd_bestc = c->sd_centers = nullptr;
-  c->sd_bsum = nullptr;
+  c->sd_bsum[0] = c->sd_bsum[1] = nullptr;
 }
 
 void free_build(kkm_ctx* c) {
@@ -1299,7 +1300,7 @@ int kkm_init_kmeanspp(kkm_ctx* c, int32_t k, const double* u, int32_t* centers_o
     if (!(u[t] >= 0.0 && u[t] < 1.0)) return fail(c, KKM_ERR_ARG, "u[%d]=%g is outside [0, 1)", t, u[t]);
   if (!c->sd_kd) {
     const size_t nb = (size_t)seed_blocks(n);
-    const size_t bytes = 4 * (((size_t)n * 4 + 255) / 256 * 256) + (nb * 8 + 255) / 256 * 256 + KKM_MAX_K * 4;
+    const size_t bytes = 4 * (((size_t)n * 4 + 255) / 256 * 256) + 2 * ((nb * 8 + 255) / 256 * 256) + KKM_MAX_K * 4;
     void* base = nullptr;
     int rc = dalloc(c, &base, bytes, c->seed_allocs, "seeding scratch");
     if (rc) return rc;
@@ -1310,23 +1311,19 @@ int kkm_init_kmeanspp(kkm_ctx* c, int32_t k, const double* u, int32_t* centers_o
       return (void*)r;
     };
     c->sd_kd = (float*)take((size_t)n * 4);
-    c->sd_D = (float*)take((size_t)n * 4);
-    c->sd_best = (float*)take((size_t)n * 4);
+    c->sd_D[0] = (float*)take((size_t)n * 4);
+    c->sd_D[1] = (float*)take((size_t)n * 4);
     c->sd_bestc = (int*)take((size_t)n * 4);
-    c->sd_bsum = (double*)take(nb * 8);
+    c->sd_bsum[0] = (double*)take(nb * 8);
+    c->sd_bsum[1] = (double*)take(nb * 8);
     c->sd_centers = (int*)take((size_t)KKM_MAX_K * 4);
   }
   const int c_first = (int)std::min<int64_t>((int64_t)std::floor(u[0] * (double)n), n - 1);
   for (int t = 0; t < k; ++t) {
-    if (t > 0) {
-      int rc = run(c, KKM_PHASE_SEED, "kpp_select", [&] {
-        return launch_kpp_select(c->sd_D, c->sd_bsum, n, u[t], c->sd_centers, t, c->stream);
-      });
-      if (rc) return rc;
-    }
-    int rc = run(c, KKM_PHASE_SEED, "kpp_dist", [&] {
-      return launch_kpp_dist(c->Xp, n, c->sz.d_pad, c->kp, c->sd_centers, t, c_first, c->sd_kd, c->sd_D,
-                             c->sd_best, c->sd_bestc, c->sd_bsum, t == k - 1 ? V : nullptr, c->stream);
+    int rc = run(c, KKM_PHASE_SEED, "kpp_pass", [&] {
+      return launch_kpp_pass(c->Xp, n, c->sz.d_pad, c->kp, c->sd_centers, t, c_first, u[t], c->sd_D[(t + 1) & 1],
+                             c->sd_bsum[(t + 1) & 1], c->sd_kd, c->sd_D[t & 1], c->sd_bestc, c->sd_bsum[t & 1],
+                             t == k - 1 ? V : nullptr, c->stream);
     });
     if (rc) return rc;
   }

@@ -231,15 +231,13 @@ hipError_t launch_cols_zpart(const float* E, const int* cl, int64_t m, int k, do
 // A block's partial E (ncol x k, point-major) from the SpMM's chunk partials.
 hipError_t launch_block_out(const IterBufs& b, float* E_out, hipStream_t s);
 hipError_t launch_trace(const float* diagK, int64_t n, double* trK, hipStream_t s);
-// K-means++ seeding (seed.hip): one distance pass per center, one draw per
-// center after the first; buffers of n (kd, D, best, bestc) and
-// seed_blocks(n) (bsum) entries.
+// K-means++ seeding (seed.hip): one launch per center t, which draws it with ut
+// from D_in and bsum_in (t = 0: takes c_first) and writes D_out and bsum_out;
+// buffers of n (kd, D, bestc) and seed_blocks(n) (bsum) entries.
 int seed_blocks(int64_t n);
-hipError_t launch_kpp_dist(const float* Xp, int64_t n, int d_pad, const KappaParams& kp, int* centers, int t,
-                           int c_first, float* kd, float* D, float* best, int* bestc, double* bsum, int* V,
-                           hipStream_t s);
-hipError_t launch_kpp_select(const float* D, const double* bsum, int64_t n, double ut, int* centers, int t,
-                             hipStream_t s);
+hipError_t launch_kpp_pass(const float* Xp, int64_t n, int d_pad, const KappaParams& kp, int* centers, int t,
+                           int c_first, double ut, const float* D_in, const double* bsum_in, float* kd, float* D_out,
+                           int* bestc, double* bsum_out, int* V, hipStream_t s);
 hipError_t launch_fill_diag(float* diagK, int64_t n, float v, hipStream_t s);
 
 hipError_t launch_zero_ints(int* p, int64_t count, hipStream_t s);
