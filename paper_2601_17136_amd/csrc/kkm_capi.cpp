@@ -426,6 +426,12 @@ int carve_from(kkm_ctx* c, int k, void* base) {
     c->otb.bmax = (float*)take(nt * 4);
   }
   b.zpart = (double*)take((size_t)k * b.nzpart * 8);
+  b.small = c->pc1 == 0 && c->mode != KKM_MODE_ONTHEFLY && c->storage == KKM_STORE_F32 &&
+            s.n <= small_n_for(k, c->mode == KKM_MODE_RESIDENT);
+  if (b.small) {  // k n / 2 bytes of at least 4 k n
+    b.zpart = (double*)b.P;
+    b.nzpart = small_wgs(s.n);
+  }
   b.hist = (int*)take((size_t)k * s.nblk * 4);
   b.base = (int*)take((size_t)k * s.nblk * 4);
   b.off = (int*)take((size_t)(k + 1) * 4);
@@ -551,10 +557,12 @@ int ensure_ws(kkm_ctx* c, int k, int iters) {
 }
 
 // Validate ids, count cluster sizes and per-block histograms (asynchronous;
-// the status word is read at the caller's final synchronisation).
-int label_pass(kkm_ctx* c, const int32_t* V) {
+// the status word is read at the caller's final synchronisation) before that
+// many updates.
+int label_pass(kkm_ctx* c, const int32_t* V, int updates) {
   IterBufs& b = c->ib;
   int rc;
+  if (b.small && updates > 0) return KKM_OK;  // the first update's SpMM does all of it
   if ((rc = run(c, KKM_PHASE_LABELS, "zero", [&] { return launch_zero_ints(c->counts[0], b.k, c->stream); })))
     return rc;
   if ((rc = run(c, KKM_PHASE_LABELS, "zero", [&] { return launch_zero_ints(b.status, 1, c->stream); })))
@@ -576,12 +584,19 @@ int one_update(kkm_ctx* c, int t, const int* cur, int* nxt, float* z_out, float*
   int* cin = c->counts[t & 1];
   int* cout = c->counts[(t + 1) & 1];
   int rc;
-  if ((rc = run(c, KKM_PHASE_SCATTER, "scatter", [&] {
+  // (a small problem's SpMM counts the sizes itself; what the assign adds to cout is not read)
+  if (!b.small && (rc = run(c, KKM_PHASE_SCATTER, "scatter", [&] {
          return launch_scatter(b, cur, cin, cout, c->changed + t, c->stream);
        })))
     return rc;
   const int* pos = nullptr;
-  if (c->mode == KKM_MODE_RESIDENT) {
+  if (b.small) {
+    if ((rc = run(c, KKM_PHASE_SPMM, "spmm_small", [&] {
+           return launch_spmm_small((const float*)c->K, c->mode == KKM_MODE_RESIDENT, b, cur, cin, c->changed + t,
+                                    t == 0, c->stream);
+         })))
+      return rc;
+  } else if (c->mode == KKM_MODE_RESIDENT) {
     if ((rc = run(c, KKM_PHASE_SPMM, "spmm_onehot", [&] { return launch_spmm_onehot(c->K, b, c->stream); })))
       return rc;
     if ((rc = run(c, KKM_PHASE_REDUCE, "spmm_reduce", [&] { return launch_spmm_reduce(b, cur, c->stream); })))
@@ -1013,7 +1028,7 @@ int kkm_panel_spmm(kkm_ctx* c, const int32_t* cl, int32_t k, double* zpart, int3
   int rc;
   c->panel_e = false;
   if ((rc = ensure_ws(c, k, 1))) return rc;
-  if ((rc = label_pass(c, cl))) return rc;  // sizes of cl in counts[0], per-block histograms
+  if ((rc = label_pass(c, cl, 1))) return rc;  // sizes of cl in counts[0], per-block histograms
   IterBufs& b = c->ib;
   if ((rc = run(c, KKM_PHASE_SCATTER, "scatter", [&] {
          return launch_scatter(b, cl, c->counts[0], c->counts[1], c->changed, c->stream);
@@ -1075,7 +1090,7 @@ int kkm_block_spmm(kkm_ctx* c, const int32_t* cl, int32_t k, float* E_out) {
   int rc;
   c->panel_e = false;
   if ((rc = ensure_ws(c, k, 1))) return rc;
-  if ((rc = label_pass(c, cl))) return rc;  // the block's rows: sizes in counts[0], per-block histograms
+  if ((rc = label_pass(c, cl, 1))) return rc;  // the block's rows: sizes in counts[0], per-block histograms
   IterBufs& b = c->ib;
   if ((rc = run(c, KKM_PHASE_SCATTER, "scatter", [&] {
          return launch_scatter(b, cl, c->counts[0], c->counts[1], c->changed, c->stream);
@@ -1176,7 +1191,7 @@ namespace {
 int iterate_loop(kkm_ctx* c, int32_t* V, int32_t k, int32_t max_iter, double tol, int32_t* iters_done,
                  double* obj_hist) {
   int rc;
-  if ((rc = label_pass(c, V))) return rc;
+  if ((rc = label_pass(c, V, max_iter))) return rc;
   const int* cur = V;
   int t = 0, status = 0;
   double Jprev = 0.0;
@@ -1266,7 +1281,7 @@ int kkm_step(kkm_ctx* c, const int32_t* cl_in, int32_t k, float* E, float* z, fl
   if ((rc = check_ready(c, k, 1))) return rc;
   if (!cl_in) return fail(c, KKM_ERR_ARG, "cl_in is NULL");
   if ((rc = ensure_ws(c, k, 1))) return rc;
-  if ((rc = label_pass(c, cl_in))) return rc;
+  if ((rc = label_pass(c, cl_in, 1))) return rc;
   int* nxt = cl_out ? cl_out : c->clbuf[0];
   if ((rc = one_update(c, 0, cl_in, nxt, z, D))) return rc;
   if (E && (rc = run(c, KKM_PHASE_OTHER, "et_to_e", [&] { return launch_et_to_e(c->ib, c->counts[0], c->epos, E, c->stream); })))

@@ -72,6 +72,21 @@ inline int sym_seg_for(int64_t n, int k) {
 constexpr int kSymMaxK = 64;
 constexpr int kSymRedStripe = 256;  // columns per workgroup of the packed reduction
 
+// Small problems (fp32 K, packed or full, no more than kSmallMaxK clusters)
+// take one SpMM kernel per update that needs no sorted points
+// (small_update.hip), up to small_n_for points.  Microseconds per update, that
+// kernel against the sorted chunks: packed, k = 8: 12 / 24 at 1000 points, 15.5 /
+// 25 at 2000, 27 / 32 at 4000, 49 / 40 at 6000; k = 64: 36 / 60 at 2000, 54 / 66
+// at 4000, 86 / 74 at 6000 (k = 40).  It reads a packed K's triangle twice and
+// its fp32 matrix product grows with the label blocks.  Full K, k = 8: 14 / 50
+// at 2000, 53 / 117 at 8000; k = 64: 34 / 39 at 2000, 113 / 79 at 8000.
+constexpr int kSmallN = 8192, kSmallMaxK = 64;
+inline int64_t small_n_for(int k, bool full) {
+  if (k > kSmallMaxK) return 0;
+  return !full ? 4096 : k <= 16 ? kSmallN : 2048;
+}
+inline int small_wgs(int64_t n) { return (int)((n + 15) / 16); }
+
 // Packed layout: row block I (rows I*kTile ..) stores columns I*kTile ..
 // ld-1 row-major with stride ld - I*kTile.  packed_row(i) is the offset of
 // the (unstored when I > 0) element (i, 0), so that (i, j) for
@@ -151,6 +166,9 @@ struct IterBufs {
   // |K(i, .)| (null for the Gaussian)
   int kf16;
   const float* kw;
+  // one SpMM kernel per update (small_update.hip); zpart then lies over P,
+  // which that kernel leaves unused
+  int small;
 };
 
 // ---------------------------------------------------------------- launchers
@@ -259,6 +277,10 @@ hipError_t launch_spmm_reduce(const IterBufs& b, const int* cl, hipStream_t s);
 // packed K (upper block triangle)
 // needs the scatter's crow and mskg for the current ids
 hipError_t launch_spmm_sym(const void* Kp, const IterBufs& b, hipStream_t s);
+// One update's E^T, self-term parts, sizes (counts) and cleared change counter
+// from the ids cl of a small problem; check: also sets the status word.
+hipError_t launch_spmm_small(const float* K, bool full, const IterBufs& b, const int* cl, int* counts,
+                             int* zero_changed, bool check, hipStream_t s);
 hipError_t launch_ecol_sum(const IterBufs& b, hipStream_t s);
 // E^T from the chunk partials (each starting at its chunk's first stored
 // column) plus the column-side sums Ecol (by point index); zpart per

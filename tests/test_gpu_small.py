@@ -1,0 +1,66 @@
+"""The one-kernel SpMM of small problems: its bounds (16-row workgroups,
+64-column batches, 16-label blocks, the largest sizes it takes and the first
+it does not), against the oracle and, over a loop, against the larger path."""
+import numpy as np
+import pytest
+
+from gpu_helpers import TOL, Engine, assignment_mismatches, rel_err, rowscaled_err
+
+pytestmark = pytest.mark.gpu
+
+# (n, k, mode): packed up to 4096 points, full up to 8192 (k <= 16) or 2048
+SIZES = [(1, 1, "packed"), (15, 2, "packed"), (16, 16, "resident"), (17, 17, "packed"), (63, 3, "resident"),
+         (65, 32, "packed"), (129, 33, "resident"), (400, 64, "packed"), (1000, 48, "resident"), (2048, 64, "resident"),
+         (2049, 20, "resident"), (4096, 5, "packed"), (4097, 5, "packed"), (4095, 64, "packed"), (8192, 16, "resident")]
+
+
+@pytest.mark.parametrize("n,k,mode", SIZES)
+def test_step_matches_the_oracle(oracle, n, k, mode):
+    rng = np.random.default_rng(n + k)
+    X = rng.standard_normal((n, 6)).astype(np.float32) * np.exp2(rng.integers(-3, 4, (n, 1))).astype(np.float32)
+    cl = rng.integers(0, max(1, k - 1), n).astype(np.int32)  # the last cluster is empty where k > 1
+    ref = oracle.step_full(oracle.Kernel("poly", 0.5, 1.0, 2).matrix(X), cl, k)
+    with Engine(X, "poly", 0.5, 1.0, 2, mode=mode) as eng:
+        out = eng.step(cl, k)
+        again = eng.step(cl, k)
+    np.testing.assert_array_equal(out["counts"], ref["counts"])
+    # fp32 sums of at most n entries, the error of each row's largest sum
+    assert rowscaled_err(out["E"], ref["E"]) <= 1e-5 and rowscaled_err(out["D"], ref["D"]) <= TOL
+    assert rel_err(out["z"], ref["z"]) <= 1e-5
+    assignment_mismatches(out["cl"], ref["cl"], ref["D"])
+    for key in ("E", "D", "z", "cl"):
+        assert np.array_equal(out[key], again[key]), key
+
+
+@pytest.mark.parametrize("mode", ["packed", "resident"])
+def test_loop_sizes_changes_and_bad_ids(oracle, mode):
+    """Several updates with the stop test, no update at all, and an id outside
+    [0, k) reported by the call that was given it, the context still usable."""
+    import torch
+    from paper_2601_17136_amd import datagen, kkm
+    X, lab = datagen.separated_blobs(700, 8, 5, seed=2)
+    cl0 = lab.copy()
+    rng = np.random.default_rng(0)
+    cl0[rng.random(700) < 0.2] = 0
+    K = oracle.Kernel("linear", 1.0, 0.0, 1).matrix(X)
+    with Engine(X, "linear", mode=mode) as eng:
+        final, it, hist = eng.iterate(cl0, 5, 20, 0.0)
+        ids, want = cl0, []
+        for _ in range(it):
+            out = oracle.step_full(K, ids, 5)
+            want.append(out["J"])
+            ids = out["cl"]
+        assert out["changed"] == 0 and it < 20
+        np.testing.assert_array_equal(final, ids)
+        np.testing.assert_allclose(hist, want, rtol=1e-4)
+        same, it0, _ = eng.iterate(cl0, 5, 0)
+        assert it0 == 0 and np.array_equal(same, cl0)
+        for bad in (-1, 5):
+            V = torch.from_numpy(cl0).cuda()
+            V[3] = bad
+            for updates in (0, 1, 2):
+                with pytest.raises(kkm.KKMError) as e:
+                    kkm.kkm_iterate(eng.ctx, V.clone(), 5, updates)
+                assert e.value.code == kkm.KKM_ERR_DEVICE_DATA
+        again, _, _ = eng.iterate(cl0, 5, 20, 0.0)
+        np.testing.assert_array_equal(again, final)
