@@ -18,6 +18,7 @@
 #include "kkm_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace kkm {
 
@@ -33,27 +34,35 @@ __device__ inline int clamp_id(int c, int k) { return c < 0 ? 0 : (c >= k ? k - 
 //                  D(i,j) = K(i,i) - 2 E(i,j)/|L_j| + z_j         (Eq. 8 + diag K)
 //                  cl'(i) = lowest j attaining min_j D(i,j); sizes of cl'.
 // The per-block histograms (cluster-major) feed the next scatter.
-template <int MODE>
-__global__ __launch_bounds__(256) void assign_kernel(IterBufs b, const int* __restrict__ counts_in,
-                                                     const int* __restrict__ cl_in,
-                                                     const int* __restrict__ pos,
-                                                     int* __restrict__ cl_out,
-                                                     int* __restrict__ counts_out,
-                                                     int* __restrict__ changed,
-                                                     double* __restrict__ obj,
-                                                     float* __restrict__ z_out,
-                                                     float* __restrict__ D_out) {
+//
+// GR groups of 256 threads share a workgroup's kBlk points: group g takes the
+// labels of its GR-th part, and the parts meet in order.  Its time is its
+// chains of dependent loads (z's parts, the labels' entries of E): one group
+// suffices up to 16 labels; beyond, four cut the chains to a quarter.  k = 300,
+// n = 30000: 63 -> 31 us; k = 64, n = 50000: 21.6 -> 17 us.
+template <int MODE, int GR>
+__global__ __launch_bounds__(256 * GR) void assign_kernel(IterBufs b, const int* __restrict__ counts_in,
+                                                          const int* __restrict__ cl_in,
+                                                          const int* __restrict__ pos,
+                                                          int* __restrict__ cl_out,
+                                                          int* __restrict__ counts_out,
+                                                          int* __restrict__ changed,
+                                                          double* __restrict__ obj,
+                                                          float* __restrict__ z_out,
+                                                          float* __restrict__ D_out) {
   extern __shared__ double smem_d[];
-  const int k = b.k, tid = threadIdx.x;
+  constexpr int kThr = 256 * GR;
+  constexpr int kZ = GR > 1 ? 8 : 4;  // z parts in flight per thread
+  const int k = b.k, tid = threadIdx.x, pt = tid & 255, gr = tid >> 8;
   double* zd = smem_d;                 // k
   float* zf = (float*)(zd + k);        // k
   float* sc = zf + k;                  // k
   int* hist = (int*)(sc + k);          // k
 
-  for (int j = tid; j < k; j += 256) hist[j] = 0;
+  for (int j = tid; j < k; j += kThr) hist[j] = 0;
   // Loads that do not wait for z are issued first (clamped to a valid point
   // so they need no branch).
-  const int64_t i = (int64_t)blockIdx.x * kBlk + tid;
+  const int64_t i = (int64_t)blockIdx.x * kBlk + pt;
   const bool valid = i < b.n;
   const int64_t iv = valid ? i : b.n - 1;
   const int cl_i = cl_in[iv];
@@ -65,38 +74,37 @@ __global__ __launch_bounds__(256) void assign_kernel(IterBufs b, const int* __re
   }
   const int cnt0 = (MODE == 1 && tid < k) ? counts_in[tid] : 0;
   if (MODE == 1) {
-    // sum_{i in L_j} E(i, j) from the reduction's nzpart parts: for k <= 256,
-    // 256/k threads per cluster each add a fixed run of parts, and the runs
+    // sum_{i in L_j} E(i, j) from the reduction's nzpart parts: for k <= kThr,
+    // kThr/k threads per cluster each add a fixed run of parts, and the runs
     // are added in order (a short latency chain instead of nzpart loads)
-    __shared__ double zrun[256];
-    const int G = k <= 256 ? 256 / k : 1;
-    if (k <= 256) {
-      const int j = tid / G, g = tid % G;
+    __shared__ double zrun[kThr];
+    auto add_parts = [&](int j, int lo, int hi) {
+      const double* zp = b.zpart + (int64_t)j * b.nzpart;
       double s = 0.0;
-      if (j < k) {
-        const int per = (b.nzpart + G - 1) / G, lo = g * per, hi = min(b.nzpart, lo + per);
-        const double* zp = b.zpart + (int64_t)j * b.nzpart;
-        for (int x = lo; x < hi; x += 4) {  // four loads in flight, added in order
-          double v[4];
+      for (int x = lo; x < hi; x += kZ) {  // kZ loads in flight, added in order
+        double v[kZ];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = zp[min(x + u, hi - 1)];
+        for (int u = 0; u < kZ; ++u) v[u] = zp[min(x + u, hi - 1)];
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (x + u < hi) s += v[u];
-        }
+        for (int u = 0; u < kZ; ++u)
+          if (x + u < hi) s += v[u];
       }
-      zrun[tid] = s;
+      return s;
+    };
+    const int G = k <= kThr ? kThr / k : 1;
+    if (k <= kThr) {
+      const int j = tid / G, g = tid % G, per = (b.nzpart + G - 1) / G, lo = g * per, hi = min(b.nzpart, lo + per);
+      zrun[tid] = j < k ? add_parts(j, lo, hi) : 0.0;
       __syncthreads();
     }
-    for (int j = tid; j < k; j += 256) {
+    for (int j = tid; j < k; j += kThr) {
       const int c = j == tid ? cnt0 : counts_in[j];
       double zs = 0.0;
       if (c > 0) {
-        if (k <= 256) {
+        if (k <= kThr) {
           for (int g = 0; g < G; ++g) zs += zrun[j * G + g];
         } else {
-          const double* zp = b.zpart + (int64_t)j * b.nzpart;
-          for (int s = 0; s < b.nzpart; ++s) zs += zp[s];
+          zs = add_parts(j, 0, b.nzpart);
         }
       }
       const double z = c > 0 ? zs / ((double)c * (double)c) : 0.0;
@@ -107,38 +115,49 @@ __global__ __launch_bounds__(256) void assign_kernel(IterBufs b, const int* __re
     }
   }
   __syncthreads();
-  if (MODE == 1 && blockIdx.x == 0 && tid == 0 && obj) {
+  if (MODE == 1 && blockIdx.x == 0 && tid < 64 && obj) {
     double s = 0.0;
-    for (int j = 0; j < k; ++j) s += zd[j];
-    *obj = *b.trK - s;  // J(cl_in) = tr K - sum_j |L_j| z_j
+    for (int j = tid; j < k; j += 64) s += zd[j];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (tid == 0) *obj = *b.trK - s;  // J(cl_in) = tr K - sum_j |L_j| z_j
   }
 
   int lab = 0, chg = 0;
-  if (valid) {
-    if (MODE == 0) {
+  if (MODE == 0) {
+    if (valid) {
       lab = cl_i;
       if (lab < 0 || lab >= k) {
         atomicOr(b.status, 1);
         lab = clamp_id(lab, k);
       }
-    } else {
-      float best = INFINITY;
-      int arg = -1;
-      for (int j0 = 0; j0 < k; j0 += 8) {
+    }
+  } else {
+    // The lowest label of the smallest distance.  A NaN is never smaller; it
+    // is taken only as the distance of the first nonempty label.
+    const int kq = (k + GR - 1) / GR, j_lo = gr * kq, j_hi = min(k, j_lo + kq);
+    float best = INFINITY;
+    int arg = -1, first = -1;
+    bool first_nan = false;
+    if (valid)
+      for (int j0 = j_lo; j0 < j_hi; j0 += 8) {
         // eight entries of E in flight (E^T has k rows, so the clamped reads
         // stay inside it); empty clusters are read but not used
         float ev[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) ev[u] = b.Et[(int64_t)min(j0 + u, k - 1) * b.ld + ei];
+        for (int u = 0; u < 8; ++u) ev[u] = b.Et[(int64_t)min(j0 + u, j_hi - 1) * b.ld + ei];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int j = j0 + u;
-          if (j < k) {
+          if (j < j_hi) {
             const float s = sc[j];
             float Dv = INFINITY;
             if (s != 0.f) {
               Dv = fmaf(s, ev[u], dg + zf[j]);
-              if (arg < 0 || Dv < best) {
+              if (GR > 1 && first < 0) {
+                first = j;
+                first_nan = Dv != Dv;
+              }
+              if (GR > 1 && arg < 0 ? Dv == Dv : arg < 0 || Dv < best) {
                 best = Dv;
                 arg = j;
               }
@@ -147,14 +166,38 @@ __global__ __launch_bounds__(256) void assign_kernel(IterBufs b, const int* __re
           }
         }
       }
+    if (GR > 1) {
+      __shared__ float bests[GR][256];
+      __shared__ int args[GR][256], firsts[GR][256];
+      bests[gr][pt] = best;
+      args[gr][pt] = arg;
+      firsts[gr][pt] = first < 0 ? -1 : 2 * first + (first_nan ? 1 : 0);
+      __syncthreads();
+      if (gr == 0) {
+#pragma unroll
+        for (int g = 1; g < GR; ++g) {
+          const int f = firsts[g][pt], a = args[g][pt];
+          if (first < 0 && f >= 0) {
+            first = f >> 1;
+            first_nan = f & 1;
+          }
+          if (a >= 0 && (arg < 0 || bests[g][pt] < best)) {
+            best = bests[g][pt];
+            arg = a;
+          }
+        }
+      }
+    }
+    if (first_nan) arg = first;
+    if (valid && gr == 0) {
       lab = arg < 0 ? 0 : arg;
       chg = (lab != clamp_id(cl_i, k));
       cl_out[i] = lab;
     }
-    atomicAdd(&hist[lab], 1);
   }
+  if (valid && gr == 0) atomicAdd(&hist[lab], 1);
   const int nchg = __syncthreads_count(chg);
-  for (int j = tid; j < k; j += 256) {
+  for (int j = tid; j < k; j += kThr) {
     const int c = hist[j];
     b.hist[(int64_t)j * b.nblk + blockIdx.x] = c;
     if (c) atomicAdd(&counts_out[j], c);
@@ -289,10 +332,13 @@ hipError_t launch_assign(int mode, const IterBufs& b, const int* counts_in, cons
   dim3 grid((unsigned)b.nblk), block(256);
   const size_t sm = assign_smem(b.k);
   if (mode == 0)
-    hipLaunchKernelGGL(assign_kernel<0>, grid, block, sm, s, b, counts_in, cl_in, pos, cl_out,
+    hipLaunchKernelGGL((assign_kernel<0, 1>), grid, block, sm, s, b, counts_in, cl_in, pos, cl_out,
+                       counts_out, changed, obj, z_out, D_out);
+  else if (b.k <= 16)
+    hipLaunchKernelGGL((assign_kernel<1, 1>), grid, block, sm, s, b, counts_in, cl_in, pos, cl_out,
                        counts_out, changed, obj, z_out, D_out);
   else
-    hipLaunchKernelGGL(assign_kernel<1>, grid, block, sm, s, b, counts_in, cl_in, pos, cl_out,
+    hipLaunchKernelGGL((assign_kernel<1, 4>), grid, dim3(1024), sm, s, b, counts_in, cl_in, pos, cl_out,
                        counts_out, changed, obj, z_out, D_out);
   return hipGetLastError();
 }
@@ -306,6 +352,10 @@ hipError_t launch_assign(int mode, const IterBufs& b, const int* counts_in, cons
 // workgroup sums the histograms it needs itself.  Workgroup 0 also writes
 // the SpMM chunk table (chunk q: cluster j, sorted positions [p0, p1), at
 // most kChunk long) and clears this update's size and change counters.
+// Its time is the chains of loads over the earlier blocks and of the offsets
+// over the clusters; with eight loads in flight and the offsets scanned by a
+// wavefront, k = 300, n = 30000 takes 22 us (59 before), k = 64, n = 100000
+// 20 (23).
 __global__ __launch_bounds__(256) void scatter_kernel(IterBufs b, const int* __restrict__ cl,
                                                       const int* __restrict__ counts,
                                                       int* __restrict__ zero_counts,
@@ -327,35 +377,73 @@ __global__ __launch_bounds__(256) void scatter_kernel(IterBufs b, const int* __r
   for (int j = tid; j < k; j += 256) cnt[j] = counts[j];
   // members of each cluster in earlier blocks: for k <= 256, 256/k threads
   // per cluster each add a run of blocks (integers: any order is exact)
+  auto before = [&](auto m_, int j, int lo, int hi) {  // members of cluster j in blocks [lo, hi), M loads in flight
+    constexpr int M = decltype(m_)::value;
+    const int* hj = b.hist + (int64_t)j * nb;
+    int s = 0;
+    for (int bb = lo; bb < hi; bb += M) {
+      int v[M];
+#pragma unroll
+      for (int u = 0; u < M; ++u) v[u] = hj[min(bb + u, hi - 1)];
+#pragma unroll
+      for (int u = 0; u < M; ++u)
+        if (bb + u < hi) s += v[u];
+    }
+    return s;
+  };
+  typedef std::integral_constant<int, 4> Few;
+  typedef std::integral_constant<int, 8> Many;
   const int G = k <= 256 ? 256 / k : 1, jg = tid / G, g = tid % G;
   if (k <= 256) {
     const int seg = (blk + G - 1) / G, lo = g * seg, hi = (lo + seg < blk) ? lo + seg : blk;
     int s = 0;
-    if (jg < k) {
-      const int* hj = b.hist + (int64_t)jg * nb;
-      for (int bb = lo; bb < hi; bb += 4) {  // four loads in flight
-        int v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = hj[min(bb + u, hi - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (bb + u < hi) s += v[u];
-      }
-    }
+    if (jg < k) s = k <= 16 ? before(Few{}, jg, lo, hi) : before(Many{}, jg, lo, hi);
     segsum[tid] = s;
   }
   __syncthreads();
-  if (tid == 0) {
-    int o = 0, q = 0;
-    for (int j = 0; j < k; ++j) {
-      const int c = cnt[j];
-      offs[j] = o;
-      qf[j] = q;
-      o += c;
-      q += (c + b.chunk_len - 1) / b.chunk_len;
+  // cluster offsets and first chunks: a serial walk of a few clusters, a scan
+  // over a wavefront of more
+  if (k <= 16) {
+    if (tid == 0) {
+      int o = 0, q = 0;
+      for (int j = 0; j < k; ++j) {
+        const int c = cnt[j];
+        offs[j] = o;
+        qf[j] = q;
+        o += c;
+        q += (c + b.chunk_len - 1) / b.chunk_len;
+      }
+      offs[k] = o;
+      qf[k] = q;
     }
-    offs[k] = o;
-    qf[k] = q;
+  } else if (w == 0) {  // lane x takes clusters per x .. per x + per - 1
+    const int per = (k + 63) / 64, j0 = min(k, lane * per), j1 = min(k, j0 + per);
+    int o = 0, q = 0;
+    for (int j = j0; j < j1; ++j) {
+      o += cnt[j];
+      q += (cnt[j] + b.chunk_len - 1) / b.chunk_len;
+    }
+    int so = o, sq = q;  // inclusive scans over the lanes
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int vo = __shfl_up(so, d, 64), vq = __shfl_up(sq, d, 64);
+      if (lane >= d) {
+        so += vo;
+        sq += vq;
+      }
+    }
+    if (lane == 63) {
+      offs[k] = so;
+      qf[k] = sq;
+    }
+    so -= o;
+    sq -= q;
+    for (int j = j0; j < j1; ++j) {
+      offs[j] = so;
+      qf[j] = sq;
+      so += cnt[j];
+      sq += (cnt[j] + b.chunk_len - 1) / b.chunk_len;
+    }
   }
   __syncthreads();
   if (k <= 256) {
@@ -366,9 +454,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(IterBufs b, const int* __r
     }
   } else {
     for (int j = tid; j < k; j += 256) {
-      int run = offs[j];
-      for (int bb = 0; bb < blk; ++bb) run += b.hist[(int64_t)j * nb + bb];
-      basej[j] = run;
+      basej[j] = offs[j] + before(Many{}, j, 0, blk);
     }
   }
   if (blk == 0) {

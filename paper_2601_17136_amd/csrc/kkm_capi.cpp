@@ -938,7 +938,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   if (mode == KKM_MODE_ONTHEFLY) {
     if ((rc = run(c, KKM_PHASE_STAGE, "diag", [&] { return launch_diag_from_norms(c->nrm, n, kp, c->diagK, c->stream); })))
       return rc;
-    return run(c, KKM_PHASE_OTHER, "trace", [&] { return launch_trace(c->diagK, n, c->trK, c->stream); });
+    return run(c, KKM_PHASE_OTHER, "trace", [&] { return launch_trace(c->diagK, n, kind == KKM_GAUSS, c->trK, c->stream); });
   }
   if (c->kw && (rc = run(c, KKM_PHASE_STAGE, "row_scales", [&] {
         return launch_row_scales(c->nrm, c->maxnrm, n, kp, c->kw, c->stream);
@@ -982,7 +982,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   if (panel && (pr0 > 0 || pr1 < n))
     return run(c, KKM_PHASE_STAGE, "diag", [&] { return launch_diag_from_norms(c->nrm, n, kp, c->diagK, c->stream); });
   if (panel) return KKM_OK;
-  return run(c, KKM_PHASE_OTHER, "trace", [&] { return launch_trace(c->diagK, n, c->trK, c->stream); });
+  return run(c, KKM_PHASE_OTHER, "trace", [&] { return launch_trace(c->diagK, n, kind == KKM_GAUSS, c->trK, c->stream); });
 }
 
 }  // namespace

@@ -64,3 +64,27 @@ def test_loop_sizes_changes_and_bad_ids(oracle, mode):
                 assert e.value.code == kkm.KKM_ERR_DEVICE_DATA
         again, _, _ = eng.iterate(cl0, 5, 20, 0.0)
         np.testing.assert_array_equal(again, final)
+
+
+@pytest.mark.parametrize("n,k", [(300, 16), (300, 17), (700, 64), (3000, 65), (3000, 301), (2000, 1024)])
+def test_assign_rule_over_label_groups(n, k):
+    """The new id is the lowest label of the smallest distance (a NaN is taken
+    only as the first nonempty label's), also where the labels are shared out
+    over four groups of threads: ties between all clusters, empty clusters at
+    the start of groups, and a point with a NaN coordinate."""
+    rng = np.random.default_rng(k)
+    X = np.ones((n, 4), np.float32)
+    X[: n // 2] = rng.integers(0, 2, (n // 2, 4))  # many exact ties
+    X[n - 1, 2] = np.nan
+    cl = rng.integers(0, k, n).astype(np.int32)
+    q = -(-k // 4)
+    cl[np.isin(cl, [0, q, 2 * q])] = min(1, k - 1)  # empty
+    with Engine(X, "linear", mode="resident") as eng:
+        out = eng.step(cl, k)
+    D, counts = out["D"], out["counts"]
+    want = np.empty(n, np.int64)
+    full = np.flatnonzero(counts > 0)
+    for i in range(n):
+        d = D[i, full]
+        want[i] = full[0] if np.isnan(d[0]) or np.isnan(d).all() else full[np.nanargmin(d)]
+    np.testing.assert_array_equal(out["cl"], want)
