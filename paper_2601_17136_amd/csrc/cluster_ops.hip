@@ -699,4 +699,30 @@ hipError_t launch_et_to_e(const IterBufs& b, const int* counts, const int* pos, 
   return hipGetLastError();
 }
 
+// Four copies of a few bytes (and of the ids) each cost the host 8-10 us and the
+// stream a launch; this is one launch.  A call of two updates with the stop
+// test on 1000 points: 138 -> 62 us.
+__global__ __launch_bounds__(256) void report_kernel(int* __restrict__ V, const int* __restrict__ cur, int64_t n,
+                                                     const double* __restrict__ obj, int t0, int count,
+                                                     const int* __restrict__ changed, const int* __restrict__ status,
+                                                     HostReport* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (V && i < n) V[i] = cur[i];
+  if (blockIdx.x == 0) {
+    for (int t = threadIdx.x; t < count; t += 256) out->obj[t] = obj[t0 + t];
+    if (threadIdx.x == 0) {
+      out->changed = changed ? *changed : 0;
+      out->status = *status;
+    }
+  }
+}
+
+hipError_t launch_report(int* V, const int* cur, int64_t n, const double* obj, int t0, int count, const int* changed,
+                         const int* status, HostReport* out, hipStream_t s) {
+  if (count > kReportObj) return hipErrorInvalidValue;
+  const unsigned grid = V ? (unsigned)((n + 255) / 256) : 1u;
+  hipLaunchKernelGGL(report_kernel, dim3(grid), dim3(256), 0, s, V, cur, n, obj, t0, count, changed, status, out);
+  return hipGetLastError();
+}
+
 }  // namespace kkm

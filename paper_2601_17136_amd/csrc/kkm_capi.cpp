@@ -209,6 +209,7 @@ struct kkm_ctx {
   int *sd_bestc = nullptr, *sd_centers = nullptr;
   double* sd_bsum[2] = {nullptr, nullptr};
 
+  HostReport* report = nullptr;  // pinned host memory, from the first kkm_iterate or kkm_step on (may stay null)
   void* scratch = nullptr;  // this device's static scratch (kkm_iterate_noalloc)
 
   int32_t timing = 0;  // mask of timed phases
@@ -573,6 +574,14 @@ int label_pass(kkm_ctx* c, const int32_t* V, int updates) {
   });
 }
 
+// The pinned report page; without one the values are copied one by one.
+void ensure_report(kkm_ctx* c) {
+  void* p = nullptr;
+  if (c->report) return;
+  if (hipHostMalloc(&p, sizeof(HostReport), hipHostMallocDefault) == hipSuccess) c->report = (HostReport*)p;
+  else (void)hipGetLastError();
+}
+
 int status_error(kkm_ctx* c, int status) {
   if (status & 1) return fail(c, KKM_ERR_DEVICE_DATA, "a cluster id is outside [0, %d)", c->ib.k);
   return KKM_OK;
@@ -784,6 +793,7 @@ int kkm_destroy(kkm_ctx* c) {
   collect_timing(c);
   free_build(c);
   for (hipEvent_t e : c->pool) (void)hipEventDestroy(e);
+  if (c->report) (void)hipHostFree(c->report);
   delete c;
   return KKM_OK;
 }
@@ -1202,10 +1212,19 @@ int iterate_loop(kkm_ctx* c, int32_t* V, int32_t k, int32_t max_iter, double tol
     if (tol >= 0.0) {
       int chg = 0;
       double J = 0.0;
-      HIP_TRY(c, hipMemcpyAsync(&chg, c->changed + t, sizeof chg, hipMemcpyDeviceToHost, c->stream), "read changes");
-      HIP_TRY(c, hipMemcpyAsync(&J, c->obj + t, sizeof J, hipMemcpyDeviceToHost, c->stream), "read objective");
-      HIP_TRY(c, hipMemcpyAsync(&status, c->ib.status, sizeof status, hipMemcpyDeviceToHost, c->stream), "read status");
-      HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+      if (c->report) {
+        HIP_TRY(c, launch_report(nullptr, nullptr, 0, c->obj, t, 1, c->changed + t, c->ib.status, c->report, c->stream),
+                "report");
+        HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+        chg = c->report->changed;
+        J = c->report->obj[0];
+        status = c->report->status;
+      } else {
+        HIP_TRY(c, hipMemcpyAsync(&chg, c->changed + t, sizeof chg, hipMemcpyDeviceToHost, c->stream), "read changes");
+        HIP_TRY(c, hipMemcpyAsync(&J, c->obj + t, sizeof J, hipMemcpyDeviceToHost, c->stream), "read objective");
+        HIP_TRY(c, hipMemcpyAsync(&status, c->ib.status, sizeof status, hipMemcpyDeviceToHost, c->stream), "read status");
+        HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+      }
       if ((rc = status_error(c, status))) return rc;
       bool stop = chg == 0;
       if (!stop && tol > 0.0 && t > 0 && (Jprev - J) <= tol * std::fabs(Jprev)) stop = true;
@@ -1216,13 +1235,21 @@ int iterate_loop(kkm_ctx* c, int32_t* V, int32_t k, int32_t max_iter, double tol
       }
     }
   }
-  if (t > 0)
-    HIP_TRY(c, hipMemcpyAsync(V, cur, (size_t)c->sz.n * 4, hipMemcpyDeviceToDevice, c->stream), "copy ids");
-  if (obj_hist && t > 0)
-    HIP_TRY(c, hipMemcpyAsync(obj_hist, c->obj, (size_t)t * sizeof(double), hipMemcpyDeviceToHost, c->stream),
-            "read objective history");
-  HIP_TRY(c, hipMemcpyAsync(&status, c->ib.status, sizeof status, hipMemcpyDeviceToHost, c->stream), "read status");
-  HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+  if (c->report && t <= kReportObj) {
+    HIP_TRY(c, launch_report(t > 0 ? V : nullptr, cur, c->sz.n, c->obj, 0, t, nullptr, c->ib.status, c->report,
+                             c->stream), "report");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+    if (obj_hist) std::memcpy(obj_hist, c->report->obj, (size_t)t * sizeof(double));
+    status = c->report->status;
+  } else {
+    if (t > 0)
+      HIP_TRY(c, hipMemcpyAsync(V, cur, (size_t)c->sz.n * 4, hipMemcpyDeviceToDevice, c->stream), "copy ids");
+    if (obj_hist && t > 0)
+      HIP_TRY(c, hipMemcpyAsync(obj_hist, c->obj, (size_t)t * sizeof(double), hipMemcpyDeviceToHost, c->stream),
+              "read objective history");
+    HIP_TRY(c, hipMemcpyAsync(&status, c->ib.status, sizeof status, hipMemcpyDeviceToHost, c->stream), "read status");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+  }
   if ((rc = status_error(c, status))) return rc;
   if (iters_done) *iters_done = t;
   return KKM_OK;
@@ -1239,6 +1266,7 @@ int kkm_iterate(kkm_ctx* c, int32_t* V, int32_t k, int32_t max_iter, double tol,
   if (!V) return fail(c, KKM_ERR_ARG, "V is NULL");
   if (iters_done) *iters_done = 0;
   if ((rc = ensure_ws(c, k, max_iter))) return rc;
+  ensure_report(c);
   return iterate_loop(c, V, k, max_iter, tol, iters_done, obj_hist);
 }
 
@@ -1281,6 +1309,7 @@ int kkm_step(kkm_ctx* c, const int32_t* cl_in, int32_t k, float* E, float* z, fl
   if ((rc = check_ready(c, k, 1))) return rc;
   if (!cl_in) return fail(c, KKM_ERR_ARG, "cl_in is NULL");
   if ((rc = ensure_ws(c, k, 1))) return rc;
+  ensure_report(c);
   if ((rc = label_pass(c, cl_in, 1))) return rc;
   int* nxt = cl_out ? cl_out : c->clbuf[0];
   if ((rc = one_update(c, 0, cl_in, nxt, z, D))) return rc;
@@ -1290,9 +1319,16 @@ int kkm_step(kkm_ctx* c, const int32_t* cl_in, int32_t k, float* E, float* z, fl
     HIP_TRY(c, hipMemcpyAsync(counts_out, c->counts[0], (size_t)k * 4, hipMemcpyDeviceToDevice, c->stream), "copy counts");
   double Jv = 0.0;
   int status = 0;
-  HIP_TRY(c, hipMemcpyAsync(&Jv, c->obj, sizeof(double), hipMemcpyDeviceToHost, c->stream), "read objective");
-  HIP_TRY(c, hipMemcpyAsync(&status, c->ib.status, sizeof status, hipMemcpyDeviceToHost, c->stream), "read status");
-  HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+  if (c->report) {
+    HIP_TRY(c, launch_report(nullptr, nullptr, 0, c->obj, 0, 1, nullptr, c->ib.status, c->report, c->stream), "report");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+    Jv = c->report->obj[0];
+    status = c->report->status;
+  } else {
+    HIP_TRY(c, hipMemcpyAsync(&Jv, c->obj, sizeof(double), hipMemcpyDeviceToHost, c->stream), "read objective");
+    HIP_TRY(c, hipMemcpyAsync(&status, c->ib.status, sizeof status, hipMemcpyDeviceToHost, c->stream), "read status");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+  }
   if ((rc = status_error(c, status))) return rc;
   if (J) *J = Jv;
   return KKM_OK;

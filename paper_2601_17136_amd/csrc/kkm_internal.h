@@ -266,6 +266,17 @@ hipError_t launch_zero_ints(int* p, int64_t count, hipStream_t s);
 hipError_t launch_assign(int mode, const IterBufs& b, const int* counts_in, const int* cl_in,
                          const int* pos, int* cl_out, int* counts_out, int* changed, double* obj,
                          float* z_out, float* D_out, hipStream_t s);
+// What the host reads of the loop, in pinned host memory: one small kernel in
+// place of a copy per value.
+constexpr int kReportObj = 500;
+struct HostReport {
+  int changed, status;
+  double obj[kReportObj];
+};
+// obj[t0 .. t0 + count), *changed and *status to the report; V (may be null)
+// takes the n ids of cur.
+hipError_t launch_report(int* V, const int* cur, int64_t n, const double* obj, int t0, int count, const int* changed,
+                         const int* status, HostReport* out, hipStream_t s);
 hipError_t launch_scatter(const IterBufs& b, const int* cl, const int* counts, int* zero_counts,
                           int* zero_changed, hipStream_t s);
 hipError_t launch_spmm_onehot(const void* K, const IterBufs& b, hipStream_t s);
