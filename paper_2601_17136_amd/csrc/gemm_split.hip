@@ -83,8 +83,9 @@ __device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, 
     }
 }
 
-// One wavefront's part of tile (I, J): rows gi0 .. gi0 + 63, columns gj0 .. gj0 + 63.  rinv, rcn: the rows' -1/s and (Gaussian)
-// c|x|^2, in LDS; cf, cnj: the columns' factor (col_factor) and c|x|^2.  est:
+// One wavefront's part of tile (I, J): rows gi0 .. gi0 + 63, columns gj0 ..
+// gj0 + 63.  rinv, rcn: the rows' -1/s and c|x|^2 (Gaussian) or |x|^2, in LDS;
+// cf, cnj: the columns' factor (col_factor) and c|x|^2.  est:
 // Gaussian entries of the tile may need the fix-up.  Tw: 32 x 65 floats of LDS
 // of the wavefront's own (mirror tiles and binary16 storage), ordered within
 // the wavefront.
@@ -167,7 +168,9 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
           const int il = bi * 32 + 8 * (r >> 2) + 4 * h + (r & 3), jl = bj * 32 + l32;
           const int64_t gi = gi0 + il, gj = gj0 + jl;
           float v = acc[bi][bj][r];
-          if (KIND == GAUSS && gi == gj) v = 1.f;  // exp(0): exact, whatever the product rounded to
+          // exp(0), or kappa of the squared norm: a square's lo lo, which the
+          // product leaves out, is never negative, so tr K would come out low (2^-25 of it)
+          if (gi == gj) v = KIND == GAUSS ? 1.f : kappa<KIND>(rcn[il], 0.f, 0.f, kp);
           if (gi >= rlim || gj >= cend) continue;
           if (gi == gj && gj < clim) o.diagK[gi] = v;
           if (!PANEL && gi > gj) continue;
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
 
   if (tid < kTile) {  // the rows' and columns' factors
     rinv[tid] = -xinv[row0 + tid];  // the product comes negated
-    rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm[row0 + tid] : 0.f;
+    rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm[row0 + tid] : nrm[row0 + tid];
   }
   float cf[2], cnj[2] = {0.f, 0.f};
 #pragma unroll

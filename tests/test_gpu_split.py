@@ -201,3 +201,16 @@ def test_on_the_fly_past_fp32_norms(d):
         ref = X64[keep] @ X64[cl == j].sum(0)
         np.testing.assert_allclose(E[keep, j], ref, rtol=1e-5)
     assert np.isinf(E[17, 2])
+
+
+@pytest.mark.parametrize("mode,d", [("packed", 25), ("packed", 54), ("packed", 301), ("resident", 784)])
+def test_diagonal_has_no_bias(mode, d):
+    """tr K, and with it the objective, sees the mean error of the diagonal.  Rounded norms of random sign leave
+    2^-25 / sqrt(n) = 2^-30.5 of it at n = 2000; the bound is 2^-28 (a square without its lo lo is low by about 2^-25)."""
+    _torch_cuda()
+    X = np.random.default_rng(d).random((2000, d), dtype=np.float32)
+    with Engine(X, "linear", mode=mode) as eng:
+        K, diag = eng.K_rows(), eng.diag().astype(np.float64)
+    ref = (X.astype(np.float64) ** 2).sum(1)
+    assert np.array_equal(np.diag(K), diag)
+    assert abs(np.mean((diag - ref) / ref)) <= 2.0 ** -28
