@@ -27,6 +27,10 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, 8 TB/s
 FP32_MFMA_PEAK_TF = 157.3    # MI355X dense fp32 matrix peak
+# From SPLIT_MIN_DPAD padded coordinates up the products run on the binary16
+# matrix cores (2.5 PFLOP/s dense), three of their products per fp32 one.
+SPLIT_MFMA_PEAK_TF = 2500.0 / 3
+SPLIT_MIN_DPAD = 32
 METRIC = "clustering iters/sec + K-build TFLOP/s, % of HBM / MFMA peak, 1 GPU"
 
 # HBM bytes per launch from two rocprofv3 counter runs (FETCH_SIZE, then
@@ -39,25 +43,12 @@ TRAFFIC = {
     # workload 2 (n=20000, d=784)
     ("spmm_sym", 2, "packed"): (("csrc/spmm_sym.hip",), ("891ad7dd7a334b15",), 397407.718, 21343.150),
     ("spmm_sym", 2, "packed-f16"): (("csrc/spmm_sym.hip",), ("891ad7dd7a334b15",), 198961.010, 21342.954),
-    ("spmm_onehot", 2, "resident"): (("csrc/cluster_ops.hip",), ("ffc98cf809a2ba97",), 782834.6, 1578.0),
     # workload 3 (n=60000, d=780)
     ("spmm_sym", 3, "packed"): (("csrc/spmm_sym.hip",), ("891ad7dd7a334b15",), 3529196.106, 93745.717),
-    ("spmm_onehot", 3, "resident"): (("csrc/cluster_ops.hip",), ("ffc98cf809a2ba97",), 7035962.829, 14074.69),
-    ("gemm_kappa", 3, "packed"): (("csrc/gemm_kappa.hip", "csrc/tile_mma.h"),
-                                  ("cd3f5d45226675f0", "366f902efcd9e5e8"), 22316348.562, 7053978.375),
-    ("gemm_kappa", 3, "resident"): (("csrc/gemm_kappa.hip", "csrc/tile_mma.h"),
-                                    ("cd3f5d45226675f0", "366f902efcd9e5e8"), 22302415.188, 14070234.375),
     # workload 4 (n=100000, d=128, k=64)
     ("spmm_sym", 4, "packed"): (("csrc/spmm_sym.hip",), ("891ad7dd7a334b15",), 9801771.536, 361881.540),
-    ("gemm_kappa", 4, "packed"): (("csrc/gemm_kappa.hip", "csrc/tile_mma.h"),
-                                  ("cd3f5d45226675f0", "366f902efcd9e5e8"), 9804441.500, 19721405.719),
     # workload 5 (n=200000, d=54)
     ("spmm_sym", 5, "packed"): (("csrc/spmm_sym.hip",), ("891ad7dd7a334b15",), 39117459.279, 886687.096),
-    ("spmm_onehot", 5, "resident"): (("csrc/cluster_ops.hip",), ("ffc98cf809a2ba97",), 78128224.638, 153234.375),
-    ("gemm_kappa", 5, "packed"): (("csrc/gemm_kappa.hip", "csrc/tile_mma.h"),
-                                  ("cd3f5d45226675f0", "366f902efcd9e5e8"), 2543482.312, 78225773.438),
-    ("gemm_kappa", 5, "resident"): (("csrc/gemm_kappa.hip", "csrc/tile_mma.h"),
-                                    ("cd3f5d45226675f0", "366f902efcd9e5e8"), 2530310.188, 156250781.250),
 }
 
 
@@ -73,6 +64,13 @@ def counted_traffic(kernel, cfg, mode):
         if hashlib.sha256(open(path, "rb").read()).hexdigest()[:16] != h:
             return None
     return round((fetch_kib * FETCH_SCALE + write_kib * WRITE_SCALE) * 1024 / 1e9, 4)
+
+
+def product_kernel(name, d):
+    """(kernel, its matrix peak) of the X X^T products at this width."""
+    split = (d + 7) // 8 * 8 >= SPLIT_MIN_DPAD
+    return ({"build": "gemm_split", "sweep": "onthefly_split"} if split else
+            {"build": "gemm_kappa", "sweep": "onthefly"})[name], SPLIT_MFMA_PEAK_TF if split else FP32_MFMA_PEAK_TF
 
 
 def time_seeding(kkm, ctx, n, k, d_pad, reps=5):
@@ -95,7 +93,7 @@ def time_seeding(kkm, ctx, n, k, d_pad, reps=5):
         ms.append(a.elapsed_time(b))
     t = min(ms)
     gbs = k * n * d_pad * 4 / (t * 1e-3) / 1e9
-    return {"ms": round(t, 4), "k": k, "launches": 2 * k - 1, "bound": "hbm", "achieved": round(gbs, 1),
+    return {"ms": round(t, 4), "k": k, "launches": k, "bound": "hbm", "achieved": round(gbs, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
             "work": "k passes over the staged points, n * d_pad * 4 bytes each"}
 
@@ -293,7 +291,8 @@ def roofline_fields(args, w, mode, res):
     flops = float(n) * (n + 1) * d                     # symmetric half of X X^T, 2 flops per MAC
     out["kbuild_ms"] = round(kbuild_ms, 4)
     out["kbuild_tflops"] = round(flops / (gemm_ms * 1e-3) / 1e12, 3) if gemm_cnt else None
-    out["kbuild_frac_mfma"] = round(out["kbuild_tflops"] / FP32_MFMA_PEAK_TF, 4) if out["kbuild_tflops"] else None
+    gname, mfma_peak = product_kernel("build", d)
+    out["kbuild_frac_mfma"] = round(out["kbuild_tflops"] / mfma_peak, 4) if out["kbuild_tflops"] else None
     # per update: the uninstrumented loop (a launch bracketed by events costs
     # a few us of stream time, which counts on the small workloads), and the
     # sum of the bracketed launches of one job
@@ -320,19 +319,20 @@ def roofline_fields(args, w, mode, res):
     else:
         otf_ms, otf_cnt = avg("onthefly")
         otf_tf = flops / (otf_ms * 1e-3) / 1e12   # the symmetric half, per update
-        out["roofline"] = {"kernel": "onthefly", "bound": "mfma", "achieved": round(otf_tf, 2),
-                           "peak": FP32_MFMA_PEAK_TF, "unit": "TFLOP/s",
-                           "frac": round(otf_tf / FP32_MFMA_PEAK_TF, 4),
-                           "traffic": counted_traffic("onthefly", w.cfg, mode),
+        oname, _ = product_kernel("sweep", d)
+        out["roofline"] = {"kernel": oname, "bound": "mfma", "achieved": round(otf_tf, 2),
+                           "peak": round(mfma_peak, 1), "unit": "TFLOP/s",
+                           "frac": round(otf_tf / mfma_peak, 4),
+                           "traffic": counted_traffic(oname, w.cfg, mode),
                            "traffic_unit": "GB per launch", "avg_launch_ms": round(otf_ms, 5),
                            "launches": otf_cnt,
                            "work": "n(n+1)d flop per update (symmetric half of X X^T)"}
     tf = out["kbuild_tflops"]
     if gemm_cnt:
-        out["roofline_kbuild"] = {"kernel": "gemm_kappa", "bound": "mfma", "achieved": tf,
-                                  "peak": FP32_MFMA_PEAK_TF, "unit": "TFLOP/s",
-                                  "frac": round(tf / FP32_MFMA_PEAK_TF, 4) if tf else None,
-                                  "traffic": counted_traffic("gemm_kappa", w.cfg, mode + traffic_tag),
+        out["roofline_kbuild"] = {"kernel": gname, "bound": "mfma", "achieved": tf,
+                                  "peak": round(mfma_peak, 1), "unit": "TFLOP/s",
+                                  "frac": round(tf / mfma_peak, 4) if tf else None,
+                                  "traffic": counted_traffic(gname, w.cfg, mode + traffic_tag),
                                   "traffic_unit": "GB per launch", "avg_launch_ms": round(gemm_ms, 5),
                                   "work": "n(n+1)d flop (symmetric half of X X^T)",
                                   "gauss_fixups": res["info"]["fixups"]}
@@ -544,6 +544,7 @@ def panel_main(args, w, X, cl0, kkm, torch):
     flops = 2.0 * n * c1 * d                   # every tile of the panel (no symmetry inside it)
     gbs = nbytes / (spmm_ms * 1e-3) / 1e9
     tf = flops / (gemm_ms * 1e-3) / 1e12
+    gname, mfma_peak = product_kernel("build", d)
     out = {"metric": "one GPU's share of a %d-GPU 1D split: updates/s of its panel" % G,
            "value": round(1e3 / upd_ms, 3), "unit": "updates/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": round(upd_ms, 4), "higher_is_better": True,
@@ -556,9 +557,9 @@ def panel_main(args, w, X, cl0, kkm, torch):
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
                         "traffic": None, "traffic_unit": "GB per launch (algorithmic %.3f)" % (nbytes / 1e9),
                         "avg_launch_ms": round(spmm_ms, 5), "launches": ph["spmm"][1]},
-           "roofline_kbuild": {"kernel": "gemm_kappa (panel)", "bound": "mfma", "achieved": round(tf, 2),
-                               "peak": FP32_MFMA_PEAK_TF, "unit": "TFLOP/s",
-                               "frac": round(tf / FP32_MFMA_PEAK_TF, 4), "avg_launch_ms": round(gemm_ms, 5),
+           "roofline_kbuild": {"kernel": gname + " (panel)", "bound": "mfma", "achieved": round(tf, 2),
+                               "peak": round(mfma_peak, 1), "unit": "TFLOP/s",
+                               "frac": round(tf / mfma_peak, 4), "avg_launch_ms": round(gemm_ms, 5),
                                "work": "2 n c1 d flop (the panel's tiles)"}}
     print(json.dumps(out), flush=True)
 
@@ -624,6 +625,7 @@ def block_main(args, w, X, cl0, kkm, torch):
     flops = 2.0 * b * b * d                    # every tile of the block
     gbs = nbytes / (spmm_ms * 1e-3) / 1e9
     tf = flops / (gemm_ms * 1e-3) / 1e12
+    gname, mfma_peak = product_kernel("build", d)
     out = {"metric": "one GPU's share of a %dx%d-GPU 1.5D split: updates/s of its block" % (Q, Q),
            "value": round(1e3 / upd_ms, 3), "unit": "updates/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": round(upd_ms, 4), "higher_is_better": True,
@@ -637,9 +639,9 @@ def block_main(args, w, X, cl0, kkm, torch):
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
                         "traffic": None, "traffic_unit": "GB per launch (algorithmic %.3f)" % (nbytes / 1e9),
                         "avg_launch_ms": round(spmm_ms, 5), "launches": ph["spmm"][1]},
-           "roofline_kbuild": {"kernel": "gemm_kappa (block)", "bound": "mfma", "achieved": round(tf, 2),
-                               "peak": FP32_MFMA_PEAK_TF, "unit": "TFLOP/s",
-                               "frac": round(tf / FP32_MFMA_PEAK_TF, 4), "avg_launch_ms": round(gemm_ms, 5),
+           "roofline_kbuild": {"kernel": gname + " (block)", "bound": "mfma", "achieved": round(tf, 2),
+                               "peak": round(mfma_peak, 1), "unit": "TFLOP/s",
+                               "frac": round(tf / mfma_peak, 4), "avg_launch_ms": round(gemm_ms, 5),
                                "work": "2 b^2 d flop (the block's tiles)"}}
     print(json.dumps(out), flush=True)
 
