@@ -62,7 +62,7 @@ hipError_t launch_row_scales(const float* nrm, const unsigned* maxnrm_bits, int6
   return hipGetLastError();
 }
 
-constexpr int64_t kOnlyInfGrid = 1024;  // workgroups of a launch beside the split build
+constexpr int64_t kBesideGrid = 1024;  // workgroups of a launch beside the split build
 
 // Four workgroups per CU (40 KB of LDS each): while some run their store
 // epilogue, others keep the matrix cores busy.  KT is the storage type of K
@@ -77,11 +77,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const unsigned* __restrict__ maxnrm_bits, int64_t n, int d_pad, int64_t ld, bool packed,
     int64_t nt, int64_t T, int64_t r0, int64_t r1, int64_t c0, int64_t c1, KappaParams kp,
     KT* __restrict__ K, const float* __restrict__ kw, float* __restrict__ diagK,
-    int2* __restrict__ fix_list, unsigned long long* __restrict__ fix_count, long long seg_cap, bool only_inf) {
+    int2* __restrict__ fix_list, unsigned long long* __restrict__ fix_count, long long seg_cap, bool beside_split) {
   constexpr bool kHalf = sizeof(KT) == 2;
   __shared__ __attribute__((aligned(16))) float lds[kLdsFloats];
   // beside the split build: only where that one does nothing
-  if (only_inf && __uint_as_float(*maxnrm_bits) < INFINITY) return;
+  if (beside_split && split_runs<KIND, PANEL>(maxnrm_bits, kp)) return;
   // No Gaussian entry can need the fix-up unless the largest norms allow it.
   const bool may_fix = KIND == GAUSS && gauss_needs_fix(1.f, __uint_as_float(*maxnrm_bits),
                                                          __uint_as_float(*maxnrm_bits), kp);
@@ -587,11 +587,11 @@ __global__ __launch_bounds__(256, 2) void gemm_kappa_sweep_kernel(
 hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,
                              int64_t n, int d_pad, int64_t ld, bool packed, bool f16, const float* kw,
                              const KappaParams& kp, void* K, float* diagK, int2* fix_list,
-                             unsigned long long* fix_count, long long seg_cap, const float* bmax, bool only_inf,
+                             unsigned long long* fix_count, long long seg_cap, const float* bmax, bool beside_split,
                              hipStream_t s) {
   if (ld >= kMaxKStride) return hipErrorInvalidValue;
   const int64_t nt = (n + kTile - 1) / kTile;
-  if (!only_inf && !f16 && d_pad <= kRegMaxDpad) {
+  if (!beside_split && !f16 && d_pad <= kRegMaxDpad) {
     if (d_pad % 8 || (kp.kind == GAUSS && !bmax)) return hipErrorInvalidValue;
     const int ns = build_sweep_segments(n);
     int64_t items = 0;
@@ -628,11 +628,11 @@ hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* 
     return hipGetLastError();
   }
   const int64_t T = nt * (nt + 1) / 2;
-  dim3 grid((unsigned)(only_inf ? std::min<int64_t>(T, kOnlyInfGrid) : T)), block(256);
+  dim3 grid((unsigned)(beside_split ? std::min<int64_t>(T, kBesideGrid) : T)), block(256);
 #define KKM_GEMM_LAUNCH(KIND, TY)                                                                        \
   hipLaunchKernelGGL((gemm_kappa_kernel<KIND, TY, false>), grid, block, 0, s, Xp, nrm, maxnrm_bits, n,     \
                      d_pad, ld, packed, nt, T, (int64_t)0, n, (int64_t)0, n, kp, (TY*)K, kw, diagK, fix_list, \
-                     fix_count, seg_cap, only_inf)
+                     fix_count, seg_cap, beside_split)
   switch (kp.kind) {
     case LINEAR:
       if (f16) KKM_GEMM_LAUNCH(LINEAR, half_t);
@@ -654,17 +654,17 @@ hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* 
 hipError_t launch_gemm_kappa_panel(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,
                                    int64_t n, int d_pad, int64_t r0, int64_t r1, int64_t c0, int64_t c1,
                                    int64_t ld, const KappaParams& kp, float* K, float* diagK, int2* fix_list,
-                                   unsigned long long* fix_count, long long seg_cap, bool only_inf, hipStream_t s) {
+                                   unsigned long long* fix_count, long long seg_cap, bool beside_split, hipStream_t s) {
   if (r0 % kTile || r1 <= r0 || r1 > n || c0 % kTile || c1 <= c0 || c1 > n || ld % kTile || ld < c1 - c0 ||
       ld >= kMaxKStride)
     return hipErrorInvalidValue;
   const int64_t nrow = (r1 - r0 + kTile - 1) / kTile, ncol = ld / kTile;
   const int64_t T = nrow * ncol;
-  dim3 grid((unsigned)(only_inf ? std::min<int64_t>(T, kOnlyInfGrid) : T)), block(256);
+  dim3 grid((unsigned)(beside_split ? std::min<int64_t>(T, kBesideGrid) : T)), block(256);
 #define KKM_PANEL_LAUNCH(KIND)                                                                           \
   hipLaunchKernelGGL((gemm_kappa_kernel<KIND, float, true>), grid, block, 0, s, Xp, nrm, maxnrm_bits, n,   \
                      d_pad, ld, false, ncol, T, r0, r1, c0, c1, kp, K, (const float*)nullptr, diagK,       \
-                     fix_list, fix_count, seg_cap, only_inf)
+                     fix_list, fix_count, seg_cap, beside_split)
   switch (kp.kind) {
     case LINEAR: KKM_PANEL_LAUNCH(LINEAR); break;
     case POLY: KKM_PANEL_LAUNCH(POLY); break;

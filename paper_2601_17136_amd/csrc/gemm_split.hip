@@ -1,8 +1,8 @@
 // K = kappa(X X^T) with the product on the binary16 matrix cores (split_mma.h):
 // the K build from kSplitMinDpad coordinates up wherever the split points are
 // held (kkm_capi.cpp), all storages, panels and blocks.  gemm_kappa.hip keeps
-// the build on the fp32 matrix cores, for fewer coordinates, for points with a
-// norm past fp32's range and for memory budgets without room for the split
+// the build on the fp32 matrix cores, for fewer coordinates, for points that
+// split_runs turns down and for memory budgets without room for the split
 // points.
 //
 // Tiles, layouts and epilogue are those of gemm_kappa.hip: the upper block
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   __shared__ __attribute__((aligned(1024))) char lds[kSplitLds > kTBytes ? kSplitLds : kTBytes];
   __shared__ __attribute__((aligned(16))) float rinv[kTile], rcn[kTile];
   const float maxnrm = __uint_as_float(*maxnrm_bits);
-  if (!(maxnrm < INFINITY)) return;  // gemm_kappa_kernel builds K then (uniform)
+  if (!split_runs<KIND, PANEL>(maxnrm_bits, kp)) return;  // gemm_kappa_kernel builds K then (uniform)
 
   // Workgroup b runs on XCD b % 8: each XCD takes a contiguous run of tiles.
   const int64_t b = blockIdx.x;

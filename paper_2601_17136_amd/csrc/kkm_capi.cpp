@@ -966,17 +966,17 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
                                  c->fix_cap / kFixSegs, kind == KKM_GAUSS ? c->bmax : nullptr, c->stream);
       })))
     return rc;
-  // without the split points, and for a norm past fp32's range (read on the device)
-  const bool only_inf = c->Xf != nullptr;
-  if ((rc = run(c, only_inf ? KKM_PHASE_OTHER : KKM_PHASE_GEMM, "gemm_kappa", [&] {
+  // without the split points, and for points that split_runs turns down (read on the device)
+  const bool beside_split = c->Xf != nullptr;
+  if ((rc = run(c, beside_split ? KKM_PHASE_OTHER : KKM_PHASE_GEMM, "gemm_kappa", [&] {
          if (panel)
            return launch_gemm_kappa_panel(c->Xp, c->nrm, c->maxnrm, n, s.d_pad, pr0, pr1, pc0, pc1, s.ld, kp,
                                           (float*)c->K, c->diagK, c->fix_list, c->fix_count,
-                                          c->fix_cap / kFixSegs, only_inf, c->stream);
+                                          c->fix_cap / kFixSegs, beside_split, c->stream);
          // the build divides by the row bounds only for binary16 storage
          return launch_gemm_kappa(c->Xp, c->nrm, c->maxnrm, n, s.d_pad, s.ld, mode == KKM_MODE_PACKED, f16,
                                   f16 ? c->kw : nullptr, kp, c->K, c->diagK, c->fix_list, c->fix_count,
-                                  c->fix_cap / kFixSegs, c->bmax, only_inf, c->stream);
+                                  c->fix_cap / kFixSegs, c->bmax, beside_split, c->stream);
        })))
     return rc;
   if (kind == KKM_GAUSS &&

@@ -185,8 +185,8 @@ struct SplitPoints {
 };
 inline size_t split_bytes(int64_t rows, int d_pad) { return (size_t)rows * ((size_t)((d_pad + 15) / 16) * 64 + 4); }
 // launch_gemm_kappa and launch_gemm_kappa_panel from the split points; they
-// build nothing when the largest squared norm is not finite (those launch
-// beside them with only_inf set).
+// build nothing where split_runs (tile_mma.h) turns the points down (those
+// launch beside them with beside_split set).
 hipError_t launch_gemm_split(const SplitPoints& sp, const float* nrm, const unsigned* maxnrm_bits, int64_t n,
                              int64_t ld, bool packed, bool f16, const float* kw, const KappaParams& kp, void* K,
                              float* diagK, int2* fix_list, unsigned long long* fix_count, long long seg_cap,
@@ -206,12 +206,12 @@ hipError_t launch_row_scales(const float* nrm, const unsigned* maxnrm_bits, int6
 hipError_t launch_blockmax(const float* nrm, int64_t nblocks, float* bmax, hipStream_t s);
 // bmax: the block maxima of nrm (launch_blockmax), read by the small-width
 // sweep for the Gaussian kernel (may be null otherwise).
-// only_inf: a small launch that builds K only when the largest squared norm
-// is not finite (beside launch_gemm_split, which then does nothing)
+// beside_split: a small launch beside launch_gemm_split that builds K only where
+// that one does nothing
 hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,
                              int64_t n, int d_pad, int64_t ld, bool packed, bool f16, const float* kw,
                              const KappaParams& kp, void* K, float* diagK, int2* fix_list,
-                             unsigned long long* fix_count, long long seg_cap, const float* bmax, bool only_inf,
+                             unsigned long long* fix_count, long long seg_cap, const float* bmax, bool beside_split,
                              hipStream_t s);
 // Recomputes the listed Gaussian entries (counts read on the device); if a
 // segment received more entries than it holds, re-tests the whole triangle.
@@ -229,7 +229,7 @@ hipError_t launch_gauss_fixup(const float* Xp, const float* nrm, int64_t n, int 
 hipError_t launch_gemm_kappa_panel(const float* Xp, const float* nrm, const unsigned* maxnrm_bits,
                                    int64_t n, int d_pad, int64_t r0, int64_t r1, int64_t c0, int64_t c1,
                                    int64_t ld, const KappaParams& kp, float* K, float* diagK, int2* fix_list,
-                                   unsigned long long* fix_count, long long seg_cap, bool only_inf, hipStream_t s);
+                                   unsigned long long* fix_count, long long seg_cap, bool beside_split, hipStream_t s);
 // D and lowest-index argmin for the panel's points (columns [b.col0, b.col0 + b.ncol))
 // from E^T (k x ld, column = point - col0), the global z and the cluster sizes;
 // counts_out gets the panel's share of the new sizes (added; zeroed by the caller).
@@ -324,12 +324,12 @@ hipError_t launch_diag_from_norms(const float* nrm, int64_t n, const KappaParams
 hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
                            const unsigned* maxnrm_bits, const IterBufs& b, int d_pad,
                            const KappaParams& kp, const OtfTables& tb, float* Epart, float* Cpart,
-                           bool only_inf, hipStream_t s);
+                           bool beside_split, hipStream_t s);
 // The gather and the sweep from the split points, d_pad >= kSplitMinDpad: xinv
 // of the staged points, Xf and xinv_s in sorted order; Xs is written (and read)
-// only where an entry may need the fix-up or a norm is not finite.  The sweep
-// does nothing when the largest squared norm is not finite: launch_onthefly
-// runs beside it with only_inf set (and makes the tables: it goes first).
+// only where the sweep or its fix-up reads it.  The sweep does nothing where
+// split_runs (tile_mma.h) turns the points down: launch_onthefly
+// runs beside it with beside_split set (and makes the tables: it goes first).
 hipError_t launch_gather_split(const float* Xp, const float* nrm, const float* xinv, const unsigned* maxnrm_bits,
                                const IterBufs& b, const int* cl, int64_t n_pad, int d_pad, const KappaParams& kp,
                                half_t* Xf, float* xinv_s, float* Xs, float* nrm_s, int* cs, hipStream_t s);

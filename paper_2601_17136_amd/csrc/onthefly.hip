@@ -206,11 +206,11 @@ __global__ __launch_bounds__(1024) void onthefly_tables_kernel(const int* __rest
 
 // FIX: the variant with the Gaussian fix-up path.  Both variants are
 // launched; each returns at once unless the largest norm calls for it.  Beside
-// the split sweep (only_inf) only the FIX variant is, and it returns at once
-// unless the largest norm is not finite.
+// the split sweep (beside_split) only the FIX variant is, and it returns at once
+// unless the split sweep does (split_runs).
 template <int KIND, bool FIX>
-__device__ inline bool sweep_runs(const unsigned* maxnrm_bits, bool only_inf, const KappaParams& kp) {
-  if (only_inf) return !(__uint_as_float(*maxnrm_bits) < INFINITY);
+__device__ inline bool sweep_runs(const unsigned* maxnrm_bits, bool beside_split, const KappaParams& kp) {
+  if (beside_split) return !split_runs<KIND, false>(maxnrm_bits, kp);
   return KIND != GAUSS || any_fix(maxnrm_bits, kp) == FIX;
 }
 
@@ -220,8 +220,8 @@ __global__ __launch_bounds__(256, 2) void onthefly_kernel(
     const unsigned* __restrict__ maxnrm_bits, const int* __restrict__ off,
     const int* __restrict__ cA, const int* __restrict__ nruns, const int64_t* __restrict__ cbase,
     int64_t n, int d_pad, int64_t ld, int nt, int nseg, int k, KappaParams kp,
-    float* __restrict__ Epart, float* __restrict__ Cpart, bool only_inf) {
-  if (!sweep_runs<KIND, FIX>(maxnrm_bits, only_inf, kp)) return;
+    float* __restrict__ Epart, float* __restrict__ Cpart, bool beside_split) {
+  if (!sweep_runs<KIND, FIX>(maxnrm_bits, beside_split, kp)) return;
   // The block's row norms sit after the mainloop buffers in the same array,
   // so the compiler reloads them per tile instead of pinning 32 registers.
   __shared__ __attribute__((aligned(16))) float lds[kLdsFloats + kTile];
@@ -453,8 +453,8 @@ __global__ __launch_bounds__(256, 2) void onthefly_reg_kernel(
     const unsigned* __restrict__ maxnrm_bits, const int* __restrict__ off,
     const int* __restrict__ cA, const int* __restrict__ nruns, const int64_t* __restrict__ cbase,
     const float* __restrict__ bmax, int64_t n, int64_t ld, int nt, int nseg, int k, KappaParams kp,
-    float* __restrict__ Epart, float* __restrict__ Cpart, bool only_inf) {
-  if (!sweep_runs<KIND, FIX>(maxnrm_bits, only_inf, kp)) return;
+    float* __restrict__ Epart, float* __restrict__ Cpart, bool beside_split) {
+  if (!sweep_runs<KIND, FIX>(maxnrm_bits, beside_split, kp)) return;
   constexpr int d_pad = 2 * HP, ldsA = 2 * HP + 4;
   __shared__ __attribute__((aligned(16))) float rn[kTile];
   __shared__ __attribute__((aligned(16))) float As[kTile * ldsA];
@@ -734,7 +734,7 @@ int64_t onthefly_cpart_floats(int64_t n, int k) {
 hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
                            const unsigned* maxnrm_bits, const IterBufs& b, int d_pad,
                            const KappaParams& kp, const OtfTables& tb, float* Epart, float* Cpart,
-                           bool only_inf, hipStream_t s) {
+                           bool beside_split, hipStream_t s) {
   const int nt = (int)((b.n + kTile - 1) / kTile), nseg = onthefly_segments(b.n);
   hipLaunchKernelGGL(onthefly_tables_kernel, dim3(1), dim3(1024), 0, s, cs, b.n, nt, tb.cA,
                      tb.nruns, tb.cbase);
@@ -743,7 +743,7 @@ hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
   int64_t items = 0;  // (segment, row block) pairs right of the diagonal
   for (int q = 0; q < nseg; ++q) items += otf_seg_begin(q + 1, nt, nseg);
   dim3 grid((unsigned)items), block(256);
-  if (d_pad <= kRegMaxDpad || only_inf) {  // (the split sweep reads the block maxima at every width)
+  if (d_pad <= kRegMaxDpad || beside_split) {  // (the split sweep reads the block maxima at every width)
     if (d_pad % 8) return hipErrorInvalidValue;
     if (kp.kind == GAUSS) {
       hipLaunchKernelGGL(blockmax_kernel, dim3((unsigned)nt), dim3(kTile), 0, s, nrm_s, tb.bmax);
@@ -754,7 +754,7 @@ hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
   if (d_pad <= kRegMaxDpad) {
 #define KKM_OTF_REG(KIND, FIX, HP)                                                                          \
   hipLaunchKernelGGL((onthefly_reg_kernel<KIND, FIX, HP>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits, b.off, \
-                     tb.cA, tb.nruns, tb.cbase, tb.bmax, b.n, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf)
+                     tb.cA, tb.nruns, tb.cbase, tb.bmax, b.n, b.ld, nt, nseg, b.k, kp, Epart, Cpart, beside_split)
 #define KKM_OTF_REG_HP(KIND, FIX)           \
   switch (d_pad / 2) {                      \
     case 4: KKM_OTF_REG(KIND, FIX, 4); break;   \
@@ -771,7 +771,7 @@ hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
     } else if (kp.kind == POLY) {
       KKM_OTF_REG_HP(POLY, false);
     } else {
-      if (!only_inf) KKM_OTF_REG_HP(GAUSS, false);
+      if (!beside_split) KKM_OTF_REG_HP(GAUSS, false);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
       KKM_OTF_REG_HP(GAUSS, true);
@@ -782,18 +782,18 @@ hipError_t launch_onthefly(const float* Xs, const float* nrm_s, const int* cs,
   }
   if (kp.kind == LINEAR) {
     hipLaunchKernelGGL((onthefly_kernel<LINEAR, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, beside_split);
   } else if (kp.kind == POLY) {
     hipLaunchKernelGGL((onthefly_kernel<POLY, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, beside_split);
   } else {
-    if (!only_inf)
+    if (!beside_split)
       hipLaunchKernelGGL((onthefly_kernel<GAUSS, false>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, beside_split);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((onthefly_kernel<GAUSS, true>), grid, block, 0, s, Xs, nrm_s, cs, maxnrm_bits,
-                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, only_inf);
+                       b.off, tb.cA, tb.nruns, tb.cbase, b.n, d_pad, b.ld, nt, nseg, b.k, kp, Epart, Cpart, beside_split);
   }
   return hipGetLastError();
 }

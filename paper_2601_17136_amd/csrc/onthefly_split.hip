@@ -1,8 +1,8 @@
 // The on-the-fly update (onthefly.hip) with the product on the binary16 matrix
 // cores (split_mma.h), from kSplitMinDpad coordinates up.  Work items, tables,
 // partials and reduction are onthefly.hip's; its sweeps on the fp32 matrix
-// cores run beside this one and do nothing unless a point's norm is past
-// fp32's range, and alone where there is no room for the sorted split points.
+// cores run beside this one and do nothing where this one does its work
+// (split_runs), and alone where there is no room for the sorted split points.
 #include "split_mma.h"
 
 namespace kkm {
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256, 2) void onthefly_split_kernel(
   __shared__ __attribute__((aligned(1024))) char lds[kNarrow ? 4 * NCH * 2 * 1024 : kSplitLds];
   __shared__ __attribute__((aligned(16))) float rinv[kTile], rcn[kTile];
   const float maxnrm = __uint_as_float(*maxnrm_bits);
-  if (!(maxnrm < INFINITY)) return;  // the fp32 sweep runs
+  if (!split_runs<KIND, false>(maxnrm_bits, kp)) return;  // the fp32 sweep runs
   int s = 0;
   int64_t first = 0;  // items before segment s
   while (s + 1 < nseg && first + otf_seg_begin(s + 1, nt, nseg) <= (int64_t)blockIdx.x) {

@@ -203,6 +203,28 @@ __device__ inline bool gauss_needs_fix(float v, float nx, float ny, const KappaP
   return kp.fix_scale * (nx + ny) * v > kp.fix_tol;
 }
 
+// Whether the products of the split points (split_mma.h), where they are held,
+// build K or run the sweep; the fp32 products do otherwise.  Every kernel of
+// either kind asks this of the same words and one of the two does the work.
+//
+// Not with a squared norm past fp32's range.  And not in a Gaussian block of
+// one GPU's share (PANEL) whose points lie far from the origin against the
+// kernel's width: an entry too small to be recomputed then carries whatever its
+// product rounded to, up to fix_scale (|x|^2 + |y|^2) of itself, and a block off
+// the diagonal may hold nothing else.  E of such blocks against 64 bits, 64
+// labels on rings, n = 18168, d = 392: 1.2e-5 with fp32 products, 6e-6 with the
+// split ones, 1.3e-5 between the two, where fp32 sums of the same entries agree
+// to 1e-6; such blocks keep the fp32 products and their results.  The line is
+// ten times what standardised points reach (share of the entry: 5e-6 at d =
+// 100); over 56 drawn blocks below it the two gave E within 8e-7 of each other.
+constexpr float kSplitBlockErr = 5.0e-5f;
+template <int KIND, bool PANEL>
+__device__ inline bool split_runs(const unsigned* maxnrm_bits, const KappaParams& kp) {
+  const float m = __uint_as_float(*maxnrm_bits);
+  if (!(m < INFINITY)) return false;
+  return !(PANEL && KIND == GAUSS && kp.fix_scale * (2.f * m) > kSplitBlockErr);
+}
+
 // The Gaussian entry from b = x.y and u = c(|x|^2 + |y|^2), c = -gamma log2(e)
 // (the norms scaled once per row and column): exp2(c s) with
 // c s = -2c b + u, clamped at 0 (s >= 0).  Two operations fewer per entry
