@@ -9,7 +9,9 @@
 // v_mfma_f32_16x16x4_f32: every product is 0 or the entry itself, the sums are
 // fp32, in a fixed order.  Nothing needs the points sorted, and nothing is
 // left to reduce but the workgroups' parts of the self-terms, which the assign
-// step adds.
+// step adds.  An infinite or NaN entry must not reach the other labels as 0
+// times itself: a wavefront whose sums come out not finite takes its entries
+// once more with those set aside and added to their own label.
 #include "kkm_internal.h"
 
 namespace kkm {
@@ -36,15 +38,17 @@ __global__ __launch_bounds__(kSmallThreads) void spmm_small_kernel(const float* 
   __shared__ __attribute__((aligned(16))) unsigned char lab[kSmallN];
   __shared__ f4 part[kSmallWaves][NB][64];
   __shared__ float esum[16 * NB][17];
+  __shared__ float extra[16 * NB][17];  // infinite and NaN entries, by label and row
   __shared__ int hist[16 * NB];
   __shared__ int own[16];
-  __shared__ int bad;
+  __shared__ int bad, any_extra;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q = lane >> 4;
   const int n = (int)b.n, k = b.k, ld = (int)b.ld;
   const int r0 = (int)blockIdx.x * 16;
   const bool first = blockIdx.x == 0;  // this workgroup also counts the sizes (and checks the ids)
   if (first && tid < 16 * NB) hist[tid] = 0;
-  if (tid == 0) bad = 0;
+  if (tid == 0) bad = any_extra = 0;
+  for (int x = tid; x < 16 * NB * 17; x += kSmallThreads) (&extra[0][0])[x] = 0.f;
   if (tid < 16) own[tid] = -1;
   __syncthreads();
   int wrong = 0;
@@ -113,6 +117,31 @@ __global__ __launch_bounds__(kSmallThreads) void spmm_small_kernel(const float* 
     if (t + 2 * kSmallWaves < nbatch) load(t + 2 * kSmallWaves, v0);
     if (t + kSmallWaves < nbatch) fold(t + kSmallWaves, v1);
   }
+  bool finite = true;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) finite &= fabsf(D[nb][r]) < INFINITY;
+  if (__ballot(!finite)) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) D[nb] = f4{0.f, 0.f, 0.f, 0.f};
+    for (t = w; t < nbatch; t += kSmallWaves) {
+      load(t, v0);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = v0[g][e];
+          if (fabsf(x) < INFINITY) continue;
+          // (columns past n hold zeros; which sum of infinities and NaN comes
+          // out does not depend on their order)
+          atomicAdd(&extra[min((int)lab[64 * t + 16 * g + 4 * q + e], k - 1)][l16], x);
+          any_extra = 1;
+          v0[g][e] = 0.f;
+        }
+      fold(t, v0);
+    }
+  }
 
   // the wavefronts' sums, in order: D[nb][r] is label 16 nb + 4 q + r of row l16
 #pragma unroll
@@ -124,7 +153,10 @@ __global__ __launch_bounds__(kSmallThreads) void spmm_small_kernel(const float* 
 #pragma unroll
     for (int ww = 1; ww < kSmallWaves; ++ww) s += part[ww][nb][ln];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) esum[16 * nb + 4 * (ln >> 4) + r][ln & 15] = s[r];
+    for (int r = 0; r < 4; ++r) {
+      const int j = 16 * nb + 4 * (ln >> 4) + r, i = ln & 15;
+      esum[j][i] = any_extra ? s[r] + extra[j][i] : s[r];
+    }
   }
   __syncthreads();
   for (int x = tid; x < k * 16; x += kSmallThreads) {

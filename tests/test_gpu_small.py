@@ -66,25 +66,71 @@ def test_loop_sizes_changes_and_bad_ids(oracle, mode):
         np.testing.assert_array_equal(again, final)
 
 
+@pytest.mark.parametrize("nan", [False, True])
 @pytest.mark.parametrize("n,k", [(300, 16), (300, 17), (700, 64), (3000, 65), (3000, 301), (2000, 1024)])
-def test_assign_rule_over_label_groups(n, k):
+def test_assign_rule_over_label_groups(n, k, nan):
     """The new id is the lowest label of the smallest distance (a NaN is taken
     only as the first nonempty label's), also where the labels are shared out
     over four groups of threads: ties between all clusters, empty clusters at
-    the start of groups, and a point with a NaN coordinate."""
+    the start of groups, and a point with a NaN coordinate, whose cluster alone
+    gets NaN distances."""
     rng = np.random.default_rng(k)
     X = np.ones((n, 4), np.float32)
     X[: n // 2] = rng.integers(0, 2, (n // 2, 4))  # many exact ties
-    X[n - 1, 2] = np.nan
+    if nan:
+        X[n - 1, 2] = np.nan
     cl = rng.integers(0, k, n).astype(np.int32)
     q = -(-k // 4)
     cl[np.isin(cl, [0, q, 2 * q])] = min(1, k - 1)  # empty
     with Engine(X, "linear", mode="resident") as eng:
         out = eng.step(cl, k)
     D, counts = out["D"], out["counts"]
-    want = np.empty(n, np.int64)
     full = np.flatnonzero(counts > 0)
+    # sums of small integers: exact
+    good = np.arange(n - 1 if nan else n)
+    Z = X[good].astype(np.float64)
+    for j in full if not nan else full[full != cl[n - 1]]:
+        m = cl[good] == j
+        E = Z @ Z[m].sum(0)
+        np.testing.assert_array_equal(out["E"][good, j], E)
+        ref = (Z * Z).sum(1) - 2 * E / m.sum() + E[m].sum() / m.sum() ** 2
+        np.testing.assert_allclose(D[good, j], ref, rtol=0, atol=1e-5)
+    assert np.isnan(D[:, cl[n - 1]]).all() == nan
+    want = np.empty(n, np.int64)
     for i in range(n):
         d = D[i, full]
         want[i] = full[0] if np.isnan(d[0]) or np.isnan(d).all() else full[np.nanargmin(d)]
     np.testing.assert_array_equal(out["cl"], want)
+
+
+@pytest.mark.parametrize("n,k,mode", [(1, 1, "resident"), (40, 3, "resident"), (300, 16, "resident"), (777, 33, "packed"),
+                                      (2048, 64, "resident"), (2049, 20, "packed"), (8192, 16, "resident")])
+def test_entries_past_fp32_stay_with_their_label(n, k, mode):
+    """One point so large that its products overflow under degree 12, and one
+    with a NaN coordinate: the sums over the clusters without them are what
+    they are without those two points, the other two are infinite or NaN."""
+    rng = np.random.default_rng(n)
+    X = (0.5 + rng.random((n, 5))).astype(np.float32)
+    cl = rng.integers(0, k, n).astype(np.int32)
+    big, nan = n // 3, n - 1
+    cl[big] = 0
+    cl[nan] = k - 1
+    X[big] = 1e4
+    if n > 1:
+        X[nan, 1] = np.nan
+    with Engine(X, "poly", 0.5, 1.0, 12, mode=mode) as eng:
+        out = eng.step(cl, k)
+    keep = np.array([i for i in range(n) if i not in (big, nan)], np.int64)
+    Z = X[keep].astype(np.float64)
+    K = (0.5 * Z @ Z.T + 1) ** 12
+    ref = K @ np.eye(k)[cl[keep]]
+    clean = [j for j in range(k) if j not in (0, k - 1)]
+    E = out["E"][keep].astype(np.float64)
+    # degree 12 multiplies the product's error by 12
+    assert np.all(np.abs(E[:, clean] - ref[:, clean]) <= 2e-5 * np.abs(ref).max(1, initial=0.0, keepdims=True))
+    assert np.isinf(out["E"][big, 0]) or n == 1 or k == 1 or big == nan
+    if k > 1:
+        assert np.all(np.isnan(out["E"][:, k - 1])) and np.all(np.isnan(out["E"][nan]) | (np.bincount(cl, minlength=k) == 0))
+        # (K with the large point is some 1e44 or more: infinite)
+        assert np.all(np.isinf(out["E"][keep, 0]))
+        assert np.all(np.isfinite(out["z"][clean]))
