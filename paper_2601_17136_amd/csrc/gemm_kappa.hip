@@ -360,7 +360,8 @@ __global__ __launch_bounds__(256, 2) void gemm_kappa_sweep_kernel(
     const float* __restrict__ Xp, const float* __restrict__ nrm, const unsigned* __restrict__ maxnrm_bits,
     int64_t n, int64_t ld, int nt, int nseg, KappaParams kp, float* __restrict__ K,
     float* __restrict__ diagK, int2* __restrict__ fix_list, unsigned long long* __restrict__ fix_count,
-    long long seg_cap, const float* __restrict__ bmax) {
+    long long seg_cap, const float* __restrict__ bmax, bool beside_split) {
+  if (beside_split && split_runs<KIND, false>(maxnrm_bits, kp)) return;
   constexpr int d_pad = 2 * HP, ldsA = 2 * HP + 4;
   __shared__ __attribute__((aligned(16))) float As[kTile * ldsA];
   __shared__ float Tm[PACKED ? 1 : 4 * 32 * 65];  // per wavefront: a 32 x 64 block transposed (full storage)
@@ -591,7 +592,7 @@ hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* 
                              hipStream_t s) {
   if (ld >= kMaxKStride) return hipErrorInvalidValue;
   const int64_t nt = (n + kTile - 1) / kTile;
-  if (!beside_split && !f16 && d_pad <= kRegMaxDpad) {
+  if (!f16 && d_pad <= kRegMaxDpad) {
     if (d_pad % 8 || (kp.kind == GAUSS && !bmax)) return hipErrorInvalidValue;
     const int ns = build_sweep_segments(n);
     int64_t items = 0;
@@ -601,11 +602,12 @@ hipError_t launch_gemm_kappa(const float* Xp, const float* nrm, const unsigned* 
   do {                                                                                                       \
     if (packed)                                                                                              \
       hipLaunchKernelGGL((gemm_kappa_sweep_kernel<KIND, HP, true>), sgrid, sblock, 0, s, Xp, nrm, maxnrm_bits, \
-                         n, ld, (int)nt, ns, kp, (float*)K, diagK, fix_list, fix_count, seg_cap, bmax);        \
+                         n, ld, (int)nt, ns, kp, (float*)K, diagK, fix_list, fix_count, seg_cap, bmax,         \
+                         beside_split);                                                                       \
     else                                                                                                     \
       hipLaunchKernelGGL((gemm_kappa_sweep_kernel<KIND, HP, false>), sgrid, sblock, 0, s, Xp, nrm,             \
                          maxnrm_bits, n, ld, (int)nt, ns, kp, (float*)K, diagK, fix_list, fix_count, seg_cap,  \
-                         bmax);                                                                              \
+                         bmax, beside_split);                                                                \
   } while (0)
 #define KKM_SWEEP_HP(KIND)                     \
   switch (d_pad / 2) {                         \

@@ -174,7 +174,7 @@ struct kkm_ctx {
   int storage = KKM_STORE_F32;
   float* kw = nullptr;        // binary16 row scales (linear, polynomial), else null
   double* trK = nullptr;
-  unsigned* maxnrm = nullptr;  // bits of the largest squared norm (next to tr K)
+  unsigned* maxnrm = nullptr;  // bits of the largest squared norm, and kStatWords in all (next to tr K)
   int2* fix_list = nullptr;
   unsigned long long* fix_count = nullptr;  // kFixSegs counters
   long long fix_cap = 0;                    // entries in all segments together
@@ -932,7 +932,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     }
   }
   const SplitPoints sp{c->Xf, c->xinv, s.n_pad, (s.d_pad + 15) / 16};
-  if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, 1, c->stream); })))
+  if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, kStatWords, c->stream); })))
     return rc;
   if ((rc = run(c, KKM_PHASE_STAGE, "stage", [&] {
          return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, otf ? nullptr : c->Xf, c->xinv, c->stream);

@@ -171,9 +171,23 @@ struct IterBufs {
   int small;
 };
 
+// What staging notes about the points, kStatWords words (zero on entry) from
+// the one the kernels are handed as maxnrm_bits on.
+enum {
+  kStatNorm,  // bits of the largest squared norm
+  // only with the split points' row factors:
+  kStatHigh,  // bits of the largest coordinate's absolute value, ...
+  kStatLow,   // ... complement of the bits of the smallest that is a nonzero row's largest
+  kStatLost,  // kLostAny: some row has a coordinate the split holds to less than 2^-22 of
+              // itself (below 2^-17 of the row's largest); kLostShare: a row has many (stage.hip)
+  kStatWords
+};
+constexpr unsigned kLostAny = 1u, kLostShare = 2u;
+
 // ---------------------------------------------------------------- launchers
-// xinv (may be null): also the split points' row factors; Xf (may be null):
-// also the split points (n_pad rows), see split_mma.h
+// maxnrm_bits: kStatWords words, zero on entry.  xinv (may be null): also the
+// split points' row factors; Xf (may be null): also the split points (n_pad
+// rows), see split_mma.h
 hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
                         unsigned* maxnrm_bits, half_t* Xf, float* xinv, hipStream_t s);
 // The split points (split_mma.h): rows a multiple of 32, nch = ceil(d_pad / 16).

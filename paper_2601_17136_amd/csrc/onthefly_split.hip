@@ -13,7 +13,8 @@ namespace {
 // the fp32 sweeps run.
 __device__ inline bool reads_fp32(const unsigned* maxnrm_bits, const KappaParams& kp) {
   const float m = __uint_as_float(*maxnrm_bits);
-  return !(m < INFINITY) || (kp.kind == GAUSS && gauss_needs_fix(1.f, m, m, kp));
+  if (kp.kind == GAUSS) return !split_runs<GAUSS, false>(maxnrm_bits, kp) || gauss_needs_fix(1.f, m, m, kp);
+  return kp.kind == POLY ? !split_runs<POLY, false>(maxnrm_bits, kp) : !split_runs<LINEAR, false>(maxnrm_bits, kp);
 }
 
 }  // namespace

@@ -5,8 +5,9 @@
 // into [2^14, 2^15) (exact) and each coordinate is taken as two binary16
 // values, hi = its rounding and lo = the rest rounded.  hi + lo is the fp32
 // value itself for three coordinates of four and one unit in the last place
-// off otherwise (a coordinate below 2^-25 of the row's largest is held to
-// 2^-39 of it).  Then
+// off otherwise, down to 2^-15 of the row's largest; from there on a coordinate
+// is held to 2^-39 of the largest (points with many of those keep the fp32
+// products: split_runs).  Then
 //   s_i s_j x_i . x_j = sum_t hi hi + hi lo + lo hi   (+ lo lo, below 2^-22 of a product)
 // with exact products and fp32 sums: three v_mfma_f32_32x32x16_f16 take 16
 // coordinates, in the time of 1.5 v_mfma_f32_32x32x2_f32 (2 coordinates

@@ -12,33 +12,41 @@ namespace kkm {
 // A workgroup stages kStageBlk rows, each wavefront kStageRows at once (their
 // loads in flight together); per row, lane l sums the squares of columns l,
 // l+64, ... in order and a fixed shuffle tree adds the lanes, so the norm is
-// deterministic.  maxnrm_bits (zero on entry) receives the largest norm as its
-// IEEE bits (non-negative floats order like their bit patterns); a workgroup
-// takes the max of its rows in LDS and updates the word only when its max is
-// larger than what the word already holds.  A stale read only costs a
+// deterministic.  stat (kStatWords words, zero on entry) receives the largest
+// norm as its IEEE bits (non-negative floats order like their bit patterns); a
+// workgroup takes the max of its rows in LDS and updates the word only when its
+// max is larger than what the word already holds.  A stale read only costs a
 // redundant atomic.
 //
 // xinv (may be null): xinv[i] = 1 / s_i, the power of two that undoes row i's
 // scale in the split points (split_mma.h); Xf (may be null): those points in
 // operand order, zero past n.  The rows' largest coordinates come from the
 // same pass as the norms, and the second pass reads the staged rows back from
-// cache.
+// cache.  With xinv, stat also receives what split_runs asks about the rows'
+// ranges: a row has many coordinates that the split holds to fewer bits if they
+// are more than a sixteenth of its nonzero ones and at least three, or half.
 constexpr int kStageRows = 4;
 constexpr int kStageWaves = 4;
 constexpr int kStageBlk = 32;
+
+__device__ inline void raise_to(unsigned* word, unsigned bits) {
+  if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < bits) atomicMax(word, bits);
+}
 
 __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __restrict__ X, int64_t n,
                                                                  int d, int d_pad, int64_t n_pad,
                                                                  float* __restrict__ Xp,
                                                                  float* __restrict__ nrm,
-                                                                 unsigned* __restrict__ maxnrm_bits,
+                                                                 unsigned* __restrict__ stat,
                                                                  half_t* __restrict__ Xf,
                                                                  float* __restrict__ xinv) {
-  __shared__ float wmax[kStageWaves];
+  __shared__ float wmax[kStageWaves], whigh[kStageWaves], wlow[kStageWaves];
+  __shared__ int nnz[kStageBlk], nlost[kStageBlk];
   __shared__ float scl[kStageBlk];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t b0 = (int64_t)blockIdx.x * kStageBlk;
-  float m = 0.f;
+  if (threadIdx.x < kStageBlk) nnz[threadIdx.x] = nlost[threadIdx.x] = 0;
+  float m = 0.f, high = 0.f, low = INFINITY;
   for (int g = 0; g < kStageBlk / (kStageRows * kStageWaves); ++g) {
     const int64_t i0 = b0 + (g * kStageWaves + w) * kStageRows;
     float s[kStageRows], mx[kStageRows];
@@ -75,20 +83,33 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
         xinv[i0 + r] = __uint_as_float((unsigned)(127 - p) << 23);
       }
       m = fmaxf(m, s[r]);
+      high = fmaxf(high, mx[r]);
+      if (mx[r] > 0.f) low = fminf(low, mx[r]);
     }
   }
-  if (lane == 0) wmax[w] = m;
+  if (lane == 0) {
+    wmax[w] = m;
+    whigh[w] = high;
+    wlow[w] = low;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int q = 1; q < kStageWaves; ++q) m = fmaxf(m, wmax[q]);
-    const unsigned bits = __float_as_uint(m);
-    if (__hip_atomic_load(maxnrm_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < bits)
-      atomicMax(maxnrm_bits, bits);
+    for (int q = 1; q < kStageWaves; ++q) {
+      m = fmaxf(m, wmax[q]);
+      high = fmaxf(high, whigh[q]);
+      low = fminf(low, wlow[q]);
+    }
+    raise_to(stat + kStatNorm, __float_as_uint(m));
+    if (xinv && high > 0.f) {
+      raise_to(stat + kStatHigh, __float_as_uint(high));
+      raise_to(stat + kStatLow, ~__float_as_uint(low));
+    }
   }
-  if (!Xf) return;
+  if (!xinv) return;
   const int nch = (d_pad + 15) / 16, l = lane & 31, h = lane >> 5;
   const float sc = scl[l];
   const float* row = Xp + (b0 + l) * d_pad + 8 * h;
+  int nz = 0, lost = 0;
   for (int c = w; c < nch; c += kStageWaves) {
     float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (16 * c + 8 * h < d_pad) {  // (a multiple of 8)
@@ -96,7 +117,24 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
       v[0] = x0.x, v[1] = x0.y, v[2] = x0.z, v[3] = x0.w;
       v[4] = x1.x, v[5] = x1.y, v[6] = x1.z, v[7] = x1.w;
     }
-    split_store(v, sc, Xf + split_unit(blockIdx.x, nch, c, 0) * kUnit + lane * 8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      nz += v[e] != 0.f ? 1 : 0;
+      lost += v[e] != 0.f && fabsf(v[e] * sc) < 0x1p-3f ? 1 : 0;
+    }
+    if (Xf) split_store(v, sc, Xf + split_unit(blockIdx.x, nch, c, 0) * kUnit + lane * 8);
+  }
+  atomicAdd(&nnz[l], nz);
+  atomicAdd(&nlost[l], lost);
+  __syncthreads();
+  if (threadIdx.x < kStageBlk) {
+    nz = nnz[l];
+    lost = nlost[l];
+    const unsigned any = __ballot(lost > 0) != 0 ? kLostAny : 0u;
+    const bool many = lost > nz / 16 && (lost >= 3 || 2 * lost >= nz);
+    const unsigned bits = any | (__ballot(lost > 0 && many) != 0 ? kLostShare : 0u);
+    if (threadIdx.x == 0 && (bits & ~__hip_atomic_load(stat + kStatLost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+      atomicOr(stat + kStatLost, bits);
   }
 }
 

@@ -217,11 +217,31 @@ __device__ inline bool gauss_needs_fix(float v, float nx, float ny, const KappaP
 // to 1e-6; such blocks keep the fp32 products and their results.  The line is
 // ten times what standardised points reach (share of the entry: 5e-6 at d =
 // 100); over 56 drawn blocks below it the two gave E within 8e-7 of each other.
+//
+// And, for the linear and polynomial kernels, not with rows of wide range: a
+// coordinate below 2^-15 of its row's largest is held to 2^-39 of that largest,
+// fewer bits than fp32's, and a point without the large coordinates sees
+// nothing else of the row.  Linear K of 32 coordinates, one of them of size s
+// in a tenth of the points and 0 in the others, largest error between the two
+// groups over K's root mean square there: 2.8e-6 at s = 1e6, 4.4e-2 at 1e10,
+// against 1.2e-6 of fp32 products at any s.  A row with many such coordinates
+// (kLostShare) is turned down whatever the other points are.  A few (points of
+// random coordinates have one in some 1e5) only matter to points much smaller
+// or larger than the row: with every row's largest coordinate within
+// kSplitRange of the others', the error they leave in K(x, y) is below 2^-27
+// |y|^2 per such coordinate.  The Gaussian's exponent is a difference against
+// the squared norms, where the same error is out of sight.
 constexpr float kSplitBlockErr = 5.0e-5f;
+constexpr float kSplitRange = 4096.f;
 template <int KIND, bool PANEL>
 __device__ inline bool split_runs(const unsigned* maxnrm_bits, const KappaParams& kp) {
   const float m = __uint_as_float(*maxnrm_bits);
   if (!(m < INFINITY)) return false;
+  if (KIND != GAUSS) {
+    const unsigned lost = maxnrm_bits[kStatLost];
+    const float hi = __uint_as_float(maxnrm_bits[kStatHigh]), lo = __uint_as_float(~maxnrm_bits[kStatLow]);
+    if ((lost & kLostShare) || (lost && hi > kSplitRange * lo)) return false;
+  }
   return !(PANEL && KIND == GAUSS && kp.fix_scale * (2.f * m) > kSplitBlockErr);
 }
 

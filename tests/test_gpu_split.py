@@ -22,9 +22,10 @@ def _torch_cuda():
 def _points(n, d, seed, spread=True):
     rng = np.random.default_rng(seed)
     X = rng.standard_normal((n, d)).astype(np.float32)
-    if spread:  # row scales over 24 binary orders, a zero row, coordinates over 12 more within a row
-        X *= np.exp2(rng.integers(-12, 13, size=(n, 1))).astype(np.float32)
-        X *= np.exp2(rng.integers(-12, 1, size=(n, d))).astype(np.float32)
+    if spread:  # row scales over 8 binary orders, a zero row, coordinates over 8 more within a row
+        # (much wider ranges keep the fp32 products: the tests of wide rows below)
+        X *= np.exp2(rng.integers(-4, 5, size=(n, 1))).astype(np.float32)
+        X *= np.exp2(rng.integers(-8, 1, size=(n, d))).astype(np.float32)
         X[n // 2] = 0.0
     return X
 
@@ -214,3 +215,84 @@ def test_diagonal_has_no_bias(mode, d):
     ref = (X.astype(np.float64) ** 2).sum(1)
     assert np.array_equal(np.diag(K), diag)
     assert abs(np.mean((diag - ref) / ref)) <= 2.0 ** -28
+
+
+def _wide(case, n, d, size, seed):
+    """Points whose rows hold coordinates of very different size, such that
+    some pairs of points share only small ones."""
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    big = np.arange(n) < n // 10
+    X[:, :2] = 0.0
+    if case == "one column":  # a tenth of the points have a large coordinate the others lack
+        X[big, 0] = size * (1 + rng.random(big.sum()))
+    elif case == "two columns":  # every point has a large one, in one column or the other
+        X[big, 0] = size * (1 + rng.random(big.sum()))
+        X[~big, 1] = size * (1 + rng.random((~big).sum()))
+    elif case == "sparse":  # two nonzero coordinates, or the small one of them alone
+        X[:] = 0.0
+        X[:, 3] = 1 + rng.random(n)
+        X[big, 0] = size * (1 + rng.random(big.sum()))
+    else:  # "few": one small coordinate in ordinary rows, large points in that column alone
+        X[:, 3] = (1 + rng.random(n)) * (100.0 / size)
+        X[big] = 0.0
+        X[big, 3] = size * (1 + rng.random(big.sum()))
+    return X, big
+
+
+WIDE = [("one column", 1e6), ("one column", 1e8), ("one column", 1e12), ("two columns", 1e9), ("sparse", 1e10), ("few", 1e10)]
+
+
+@pytest.mark.parametrize("case,size", WIDE)
+@pytest.mark.parametrize("n,d", [(200, 32), (300, 130)])
+def test_rows_of_wide_range_keep_fp32_products(n, d, case, size):
+    """Every entry within what fp32 products give, relative to the sum of its
+    own terms' sizes (and not to the points' norms); K is the one that a budget
+    without room for the split points builds."""
+    _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    X, big = _wide(case, n, d, size, n + d)
+    X64 = X.astype(np.float64)
+    B, S = X64 @ X64.T, np.abs(X64) @ np.abs(X64).T
+    off = ~np.eye(n, dtype=bool)
+    for kind, mode in [("linear", "packed"), ("linear", "resident"), ("poly", "packed")]:
+        args = (kind, 1.0, 1.0, 2) if kind == "poly" else (kind,)
+        with Engine(X, *args, mode=mode) as eng:
+            K = eng.K_rows()
+        if kind == "linear":
+            assert np.all((np.abs(K - B) <= (d + 2) * 2.0 ** -24 * S)[off])
+        else:
+            ref = (B + 1) ** 2
+            ok = (np.abs(K - ref) <= 2 * (np.abs(B) + 1) * (d + 4) * 2.0 ** -24 * (S + 1)) | (ref > 1e38)
+            assert np.all(ok[off])
+        _, need = kkm.kkm_plan(n, d, 1, kkm.KINDS[kind], 1 << 40, kkm.MODES[mode])
+        with Engine(X, *args, mode=mode, mem_budget=need + 4096, k_hint=1) as eng:
+            assert np.array_equal(eng.K_rows(), K)
+
+
+@pytest.mark.parametrize("case,size", WIDE)
+@pytest.mark.parametrize("d", [32, 130])
+def test_rows_of_wide_range_on_the_fly(d, case, size):
+    """The sweep and a block of one GPU's share on the same points: sums of the
+    large points' entries over the small points' cluster."""
+    torch = _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    n = 256
+    X, big = _wide(case, n, d, size, d)
+    cl = np.where(big, 0, 1).astype(np.int32)
+    X64 = X.astype(np.float64)
+    V = np.eye(2)[cl]
+    ref, S = X64 @ (X64.T @ V), np.abs(X64) @ (np.abs(X64).T @ V)
+    bound = (d + 2 + n) * 2.0 ** -24 * S
+    other = V == 0  # the entries between the groups
+    with Engine(X, "linear", mode="onthefly") as eng:
+        E = eng.step(cl, 2)["E"]
+    assert np.all((np.abs(E - ref) <= bound)[other])
+    ctx = kkm.kkm_create(kkm.current_stream_handle())
+    try:
+        kkm.kkm_build_block(ctx, torch.from_numpy(X).cuda(), n, d, kkm.KKM_LINEAR, kkm.make_params(), 0, n, 0, n)
+        E = torch.empty((n, 2), device="cuda")
+        kkm.kkm_block_spmm(ctx, torch.from_numpy(cl).cuda(), 2, E)
+        assert np.all((np.abs(E.cpu().numpy() - ref) <= bound)[other])
+    finally:
+        kkm.kkm_destroy(ctx)
