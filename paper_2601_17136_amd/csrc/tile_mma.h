@@ -207,7 +207,9 @@ __device__ inline bool gauss_needs_fix(float v, float nx, float ny, const KappaP
 // build K or run the sweep; the fp32 products do otherwise.  Every kernel of
 // either kind asks this of the same words and one of the two does the work.
 //
-// Not with a squared norm past fp32's range.  And not in a Gaussian block of
+// Not with a squared norm past fp32's range, nor where the factor that undoes a
+// column's scale, 1/s_j times gamma or -2c (col_factor), could leave it: an
+// infinite factor makes NaN of a product of 0.  And not in a Gaussian block of
 // one GPU's share (PANEL) whose points lie far from the origin against the
 // kernel's width: an entry too small to be recomputed then carries whatever its
 // product rounded to, up to fix_scale (|x|^2 + |y|^2) of itself, and a block off
@@ -237,9 +239,13 @@ template <int KIND, bool PANEL>
 __device__ inline bool split_runs(const unsigned* maxnrm_bits, const KappaParams& kp) {
   const float m = __uint_as_float(*maxnrm_bits);
   if (!(m < INFINITY)) return false;
+  const float hi = __uint_as_float(maxnrm_bits[kStatHigh]), lo = __uint_as_float(~maxnrm_bits[kStatLow]);
+  if (hi > 0.f) {  // (1/s_j lies between lo 2^-15 and hi 2^-14)
+    const float f = KIND == GAUSS ? kp.m2c : KIND == POLY ? fabsf(kp.gamma) : 1.f;
+    if (!(f * hi < 0x1p120f && lo > 0x1p-90f && (f == 0.f || f * lo > 0x1p-90f))) return false;
+  }
   if (KIND != GAUSS) {
     const unsigned lost = maxnrm_bits[kStatLost];
-    const float hi = __uint_as_float(maxnrm_bits[kStatHigh]), lo = __uint_as_float(~maxnrm_bits[kStatLow]);
     if ((lost & kLostShare) || (lost && hi > kSplitRange * lo)) return false;
   }
   return !(PANEL && KIND == GAUSS && kp.fix_scale * (2.f * m) > kSplitBlockErr);

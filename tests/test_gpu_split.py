@@ -296,3 +296,34 @@ def test_rows_of_wide_range_on_the_fly(d, case, size):
         assert np.all((np.abs(E.cpu().numpy() - ref) <= bound)[other])
     finally:
         kkm.kkm_destroy(ctx)
+
+
+@pytest.mark.parametrize("kind,gamma,scale", [("gauss", 1e31, 1e12), ("gauss", 1e-36, 1e8), ("poly", 1e30, 1e15),
+                                              ("poly", 1e-36, 1e-3), ("linear", 1.0, 1e-30)])
+def test_factors_at_the_ends_of_fp32(kind, gamma, scale):
+    """Scales and kernel widths whose product with a row's factor leaves fp32's
+    range: K is the one that fp32 products give.  Half of the points share no
+    coordinate with the other half."""
+    _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    n, d = 200, 40
+    X = np.random.default_rng(8).random((n, d)).astype(np.float32) + np.float32(0.5)
+    X[: n // 2, 20:] = 0.0
+    X[n // 2:, :20] = 0.0
+    X *= np.float32(scale)
+    args = (kind, gamma, 0.5, 1)
+    with Engine(X, *args, mode="packed") as eng:
+        K = eng.K_rows()
+    _, need = kkm.kkm_plan(n, d, 1, kkm.KINDS[kind], 1 << 40, kkm.KKM_MODE_PACKED)
+    with Engine(X, *args, mode="packed", mem_budget=need + 4096, k_hint=1) as eng:
+        assert np.array_equal(eng.K_rows(), K, equal_nan=True)
+    X64 = X.astype(np.float64)
+    off = ~np.eye(n, dtype=bool)
+    if kind == "gauss":
+        sq = (X64 * X64).sum(1)
+        ref = np.exp(-gamma * np.maximum(sq[:, None] + sq[None] - 2 * X64 @ X64.T, 0.0))
+        assert np.all(np.abs(K - ref)[off] <= 1e-4)
+    else:
+        apart = np.zeros((n, n), bool)
+        apart[: n // 2, n // 2:] = apart[n // 2:, : n // 2] = True
+        assert np.all(K[apart] == (0.5 if kind == "poly" else 0.0))
