@@ -262,9 +262,34 @@ void release_split(kkm_ctx* c) {
   c->xinv = c->xinv_s = nullptr;
 }
 
+void free_seed(kkm_ctx* c) {
+  release(c, c->seed_allocs);
+  c->sd_kd = c->sd_D[0] = c->sd_D[1] = nullptr;
+  c->sd_bestc = c->sd_centers = nullptr;
+  c->sd_bsum[0] = c->sd_bsum[1] = nullptr;
+}
+
+size_t bytes_of(const std::vector<Alloc>& v) {
+  size_t b = 0;
+  for (const Alloc& a : v) b += a.bytes;
+  return b;
+}
+
+// Gives back what the budget cannot hold beside so many more bytes, if that
+// makes the room: the seeding scratch (the next seeding makes it again), else
+// the split points, else both.
+void make_room(kkm_ctx* c, size_t bytes, const std::vector<Alloc>& owner) {
+  if (c->held + bytes <= c->budget) return;
+  const size_t need = c->held + bytes - c->budget;
+  const size_t seed = &owner == &c->seed_allocs ? 0 : bytes_of(c->seed_allocs), split = bytes_of(c->split_allocs);
+  if (seed + split < need) return;
+  if (seed >= need || split < need) free_seed(c);
+  if (seed < need) release_split(c);
+}
+
 int dalloc(kkm_ctx* c, void** p, size_t bytes, std::vector<Alloc>& owner, const char* what) {
   bytes = std::max<size_t>(bytes, 256);
-  if (c->held + bytes > c->budget && c->Xf) release_split(c);
+  make_room(c, bytes, owner);
   if (c->held + bytes > c->budget)
     return fail(c, KKM_ERR_OOM, "%s needs %zu bytes; %zu of the %zu-byte budget already held", what,
                 bytes, c->held, c->budget);
@@ -340,13 +365,6 @@ void free_hist(kkm_ctx* c) {
   c->iter_ws = 0;
   c->changed = nullptr;
   c->obj = nullptr;
-}
-
-void free_seed(kkm_ctx* c) {
-  release(c, c->seed_allocs);
-  c->sd_kd = c->sd_D[0] = c->sd_D[1] = nullptr;
-  c->sd_bestc = c->sd_centers = nullptr;
-  c->sd_bsum[0] = c->sd_bsum[1] = nullptr;
 }
 
 void free_build(kkm_ctx* c) {
@@ -647,6 +665,12 @@ int one_update(kkm_ctx* c, int t, const int* cur, int* nxt, float* z_out, float*
   });
 }
 
+// Seeding scratch: four buffers of n entries, two of block sums, the centers.
+size_t seed_bytes(int64_t n) {
+  const size_t nb = (size_t)seed_blocks(n);
+  return 4 * (((size_t)n * 4 + 255) / 256 * 256) + 2 * ((nb * 8 + 255) / 256 * 256) + KKM_MAX_K * 4;
+}
+
 int check_ready(kkm_ctx* c, int32_t k, int32_t max_iter) {
   if (!c) return fail(nullptr, KKM_ERR_ARG, "ctx is NULL");
   if (!c->built) return fail(c, KKM_ERR_STATE, "no kernel matrix built on this context");
@@ -819,14 +843,10 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   } else {
     // plan with the caller's k hint (else k = 1 sizes the scratch and the
     // mode is picked without k): the k-dependent scratch is sized when
-    // kkm_iterate is called
-    size_t held_by_build = 0;
-    for (const Alloc& a : c->build_allocs) held_by_build += a.bytes;
-    for (const Alloc& a : c->ws_allocs) held_by_build += a.bytes;
-    for (const Alloc& a : c->hist_allocs) held_by_build += a.bytes;
-    const size_t budget_left = c->budget - std::min(c->budget, c->held - std::min(c->held, held_by_build));
+    // kkm_iterate is called.  All the context holds can make way: the last
+    // build's buffers are freed or used again.
     const int32_t kh = std::min<int64_t>(params->k_hint, n);
-    if (plan_impl(n, d, kh > 0 ? kh : 1, kh > 0, kind, budget_left, params->mode, params->storage, &mode,
+    if (plan_impl(n, d, kh > 0 ? kh : 1, kh > 0, kind, c->budget, params->mode, params->storage, &mode,
                   &need) != KKM_OK)
       return fail(c, KKM_ERR_OOM, "%s", g_noctx_err.c_str());
   }
@@ -1351,9 +1371,8 @@ int kkm_init_kmeanspp(kkm_ctx* c, int32_t k, const double* u, int32_t* centers_o
     if (!(u[t] >= 0.0 && u[t] < 1.0)) return fail(c, KKM_ERR_ARG, "u[%d]=%g is outside [0, 1)", t, u[t]);
   if (!c->sd_kd) {
     const size_t nb = (size_t)seed_blocks(n);
-    const size_t bytes = 4 * (((size_t)n * 4 + 255) / 256 * 256) + 2 * ((nb * 8 + 255) / 256 * 256) + KKM_MAX_K * 4;
     void* base = nullptr;
-    int rc = dalloc(c, &base, bytes, c->seed_allocs, "seeding scratch");
+    int rc = dalloc(c, &base, seed_bytes(n), c->seed_allocs, "seeding scratch");
     if (rc) return rc;
     char* p = (char*)base;
     auto take = [&](size_t b) {

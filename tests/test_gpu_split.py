@@ -327,3 +327,40 @@ def test_factors_at_the_ends_of_fp32(kind, gamma, scale):
         apart = np.zeros((n, n), bool)
         apart[: n // 2, n // 2:] = apart[n // 2:, : n // 2] = True
         assert np.all(K[apart] == (0.5 if kind == "poly" else 0.0))
+
+
+def test_a_rebuild_is_not_charged_for_what_it_can_free():
+    """The split points and the seeding scratch of one build make way for the
+    next on the same context, as on a new one: more points in an explicit mode,
+    more clusters announced under AUTO, the same build after seeding, and an
+    update after seeding, in budgets that hold just what kkm_plan asks for."""
+    torch = _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    d, L = 400, kkm.KKM_LINEAR
+    X = _points(1500, d, 6, spread=False)
+    Xd = torch.from_numpy(X).cuda()
+    plan = lambda n, k, mode: kkm.kkm_plan(n, d, k, L, 1 << 40, mode)[1]
+
+    need = plan(1500, 1, kkm.KKM_MODE_PACKED) + 4096
+    assert plan(600, 1, kkm.KKM_MODE_PACKED) + 640 * (d * 4 + 4) + 8192 < need
+    with Engine(X[:600], "linear", mode="packed", mem_budget=need) as eng:
+        held = eng.info()["bytes_total"]
+        assert held > 640 * (d * 4 + 4) * 2  # the split points are held
+        kkm.kkm_build_kernel(eng.ctx, Xd, 1500, d, L, kkm.make_params(mode=kkm.KKM_MODE_PACKED))
+        assert eng.info()["n"] == 1500 and eng.info()["bytes_total"] <= need
+
+    need = plan(1500, 60, kkm.KKM_MODE_PACKED) + 4096
+    assert plan(1500, 1, kkm.KKM_MODE_PACKED) + 1536 * (d * 4 + 4) + 8192 < need
+    with Engine(X, "linear", mode="auto", mem_budget=need, k_hint=1) as eng:
+        assert eng.info()["mode"] == kkm.KKM_MODE_PACKED
+        kkm.kkm_build_kernel(eng.ctx, eng.X, 1500, d, L, kkm.make_params(k_hint=60))
+        assert eng.info()["mode"] == kkm.KKM_MODE_PACKED
+        _, it, _ = eng.iterate((np.arange(1500) % 60).astype(np.int32), 60, 2)
+        assert it == 2 and eng.info()["bytes_total"] <= need
+
+    need = plan(1500, 9, kkm.KKM_MODE_PACKED) + 4096
+    with Engine(X, "linear", mode="packed", mem_budget=need, k_hint=9) as eng:
+        _, V = eng.seed(9, np.random.default_rng(0).random(9))
+        kkm.kkm_build_kernel(eng.ctx, eng.X, 1500, d, L, kkm.make_params(mode=kkm.KKM_MODE_PACKED, k_hint=9))
+        _, it, _ = eng.iterate(V, 9, 2)
+        assert it == 2 and eng.info()["bytes_total"] <= need
