@@ -222,6 +222,15 @@ int kkm_check_iterate_args(int64_t n, int32_t k, int32_t max_iter);
  * ONTHEFLY: stages X and row norms only.
  * storage F16 (RESIDENT, PACKED): K in binary16 with row scales, see
  *   kkm_storage; diag K stays fp32.
+ * From 25 features up the products of the build and of the on-the-fly update
+ *   run on the binary16 matrix cores, each coordinate as two binary16 parts with
+ *   fp32 sums, where the budget has room for the split points beside what
+ *   kkm_plan counts (4 bytes per padded coordinate and 4 to 8 per point; on the
+ *   fly also the seeding scratch); else, and for points whose range or norms
+ *   that split does not hold to fp32's accuracy, on the fp32 matrix cores.  The
+ *   last bits of K differ between the two.  On the fly the split points are
+ *   given back for good (until the next build) when a later call with more
+ *   clusters than k_hint needs their room.
  * Replaces any earlier build on ctx; a build of the same n, d, kind and mode
  * reuses the device buffers of the previous one.  Asynchronous.
  * Errors: KKM_ERR_ARG, KKM_ERR_OOM, KKM_ERR_HIP. */

@@ -932,14 +932,16 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     c->fix_count = (unsigned long long*)((char*)p + (size_t)cap * sizeof(int2));
     c->fix_cap = cap;
   }
-  // The split points, where the budget holds them beside the iteration scratch.
+  // The split points, where the budget holds them beside the iteration scratch
+  // and, on the fly, where every update takes them, the seeding scratch too.
   const bool f16 = storage == KKM_STORE_F16;
   const bool otf = mode == KKM_MODE_ONTHEFLY;
   if (s.d_pad >= kSplitMinDpad && !c->Xf) {
     const size_t split = split_bytes(s.n_pad, s.d_pad), bytes = split + (otf ? (size_t)s.n_pad * 4 : 0);
     const int32_t kh = std::min<int64_t>(params->k_hint, n);
     const size_t scratch = c->ws_allocs.empty() ? ws_bytes(c->wsz, kh > 0 ? kh : 1, mode) + 4096 : 0;
-    if (c->held + bytes + scratch <= c->budget) {
+    const size_t seed = otf && !c->sd_kd ? seed_bytes(n) : 0;
+    if (c->held + bytes + scratch + seed <= c->budget) {
       if (hipMalloc(&p, bytes) == hipSuccess) {
         c->split_allocs.push_back({p, bytes});
         c->held += bytes;

@@ -364,3 +364,26 @@ def test_a_rebuild_is_not_charged_for_what_it_can_free():
         kkm.kkm_build_kernel(eng.ctx, eng.X, 1500, d, L, kkm.make_params(mode=kkm.KKM_MODE_PACKED, k_hint=9))
         _, it, _ = eng.iterate(V, 9, 2)
         assert it == 2 and eng.info()["bytes_total"] <= need
+
+
+@pytest.mark.parametrize("spare", [0, 4096, 20000, 60000, 400000])
+def test_on_the_fly_bits_do_not_depend_on_seeding(spare):
+    """With little or no room beside the split points, the same update gives the
+    same bits before and after seeding; a request that fails takes nothing away."""
+    _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    n, d, k = 2000, 90, 7
+    X = _points(n, d, 5, spread=False)
+    cl = (np.arange(n) % k).astype(np.int32)
+    _, need = kkm.kkm_plan(n, d, k, kkm.KKM_LINEAR, 1 << 40, kkm.KKM_MODE_ONTHEFLY)
+    split = 2048 * (6 * 64 + 8)
+    with Engine(X, "linear", mode="onthefly", mem_budget=need + split + spare, k_hint=k) as eng:
+        first = eng.step(cl, k)
+        with pytest.raises(kkm.KKMError) as e:
+            eng.step((np.arange(n) % 1000).astype(np.int32), 1000, want_E=False, want_D=False)
+        assert e.value.code == kkm.KKM_ERR_OOM
+        again = eng.step(cl, k)
+        eng.seed(k, np.random.default_rng(1).random(k))
+        after = eng.step(cl, k)
+    for key in ("E", "D", "z", "cl"):
+        assert np.array_equal(first[key], again[key]) and np.array_equal(first[key], after[key]), key
