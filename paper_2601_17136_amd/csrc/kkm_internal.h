@@ -263,7 +263,7 @@ hipError_t launch_cols_zpart(const float* E, const int* cl, int64_t m, int k, do
 // A block's partial E (ncol x k, point-major) from the SpMM's chunk partials.
 hipError_t launch_block_out(const IterBufs& b, float* E_out, hipStream_t s);
 hipError_t launch_trace(const float* diagK, int64_t n, bool ones, double* trK, hipStream_t s);
-// K-means++ seeding (seed.hip): one launch per center t, which draws it with ut
+// K-means++ seeding (seed.hip): the pass of center t, which draws it with ut
 // from D_in and bsum_in (t = 0: takes c_first) and writes D_out and bsum_out;
 // buffers of n (kd, D, bestc) and seed_blocks(n) (bsum) entries.
 int seed_blocks(int64_t n);

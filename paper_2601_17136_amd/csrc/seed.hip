@@ -11,13 +11,16 @@
 //
 // The entries of K are computed from the staged points, whatever the K
 // storage mode, and the three entries of a distance by the same routine, so
-// a point that coincides with a center has distance exactly 0.  One launch per
-// center: every workgroup first walks the prefix sums of D to the drawn index
-// (the same index in each: a fixed order over the same values), then updates D
-// and the nearest center (lowest position on ties) of its points and writes
-// their fp64 sum of D.  D and its sums alternate between two buffers, so that
-// no workgroup overwrites what another still draws from.  Nothing returns to
-// the host between centers.
+// a point that coincides with a center has distance exactly 0.  One pass per
+// center updates D and the nearest center (lowest position on ties) of the
+// points and writes their fp64 sums of D per block.  Up to kSeedFusedBlk blocks
+// it is one launch: every workgroup first walks the prefix sums of D to the
+// drawn index (the same index in each: a fixed order over the same values).  D
+// and its sums alternate between two buffers, so that no workgroup overwrites
+// what another still draws from.  The sums are then read once per workgroup, 8
+// (n / 64)^2 bytes per center, so beyond that one workgroup draws in a launch of
+// its own.  Nothing returns to the host between centers.
+#include "kkm.h"
 #include "tile_mma.h"
 
 namespace kkm {
@@ -28,6 +31,13 @@ constexpr int kSeedThr = 256;               // threads per workgroup
 constexpr int kSeedLanes = 16;              // lanes per point
 constexpr int kSeedPer = 4;                 // points per group of lanes, their loads in flight together
 constexpr int kSeedPts = kSeedThr / kSeedLanes * kSeedPer;  // points per workgroup (one block of D)
+
+// Microseconds per center, drawn in the pass / by a launch before it: 50000
+// points 9.5 / 10.4 (d = 8), 33.4 / 35.0 (d = 784); 100000 points 11.4 / 10.6,
+// 16.1 / 16.5 (d = 128), 62.0 / 63.0; 200000 points 18.7 / 12.7, 25.6 / 24.0;
+// 1000000 points 225 / 33, 301 / 104.  The sums come once per workgroup, so the
+// first grows with n^2.
+constexpr int kSeedFusedBlk = 1600;
 
 // The dot products x_i . x_c (or, for the Gaussian, |x_i - x_c|^2) of
 // kSeedPer rows over d_pad floats, by a group of 16 lanes: lane l takes the
@@ -78,21 +88,28 @@ __device__ inline float kentry(float s, const KappaParams& kp) {
   return kappa<KIND>(s, 0.f, 0.f, kp);
 }
 
-// The lowest index not among centers[0 .. t-1] (one thread).
-__device__ inline int lowest_unused(const int* __restrict__ centers, int t, int64_t n) {
-  for (int64_t i = 0; i < n; ++i) {
-    bool used = false;
-    for (int s2 = 0; s2 < t; ++s2) used |= (centers[s2] == (int)i);
-    if (!used) return (int)i;
-  }
-  return -1;
-}
-
 // LDS of a draw.
 struct DrawLds {
   double wsum[kSeedThr / 64], val;
   int vote[kSeedThr / 64], index;
+  unsigned char used[KKM_MAX_K];
 };
+
+// The lowest index not among centers[0 .. t-1]; it is at most t (< n).  All
+// threads call.
+__device__ inline int lowest_unused(const int* __restrict__ centers, int t, DrawLds& x) {
+  const int tid = threadIdx.x;
+  for (int i = tid; i < t; i += kSeedThr) x.used[i] = 0;
+  if (tid == 0) x.index = t;
+  __syncthreads();
+  for (int i = tid; i < t; i += kSeedThr)
+    if (centers[i] < t) x.used[centers[i]] = 1;
+  __syncthreads();
+  for (int i = tid; i < t; i += kSeedThr)
+    if (!x.used[i]) atomicMin(&x.index, i);
+  __syncthreads();
+  return x.index;
+}
 
 // Inclusive prefix sums of v over the workgroup's threads: a fixed shuffle
 // tree per wavefront, then the wavefronts' totals in order.
@@ -201,12 +218,16 @@ __device__ inline int draw_center(const float* __restrict__ D, const double* __r
     if (f < 0) f = block_vote(d > 0.f, false, x);
     if (f >= 0) index = (int)(i0 + f);
   }
-  if (index < 0) {
-    if (tid == 0) x.index = lowest_unused(centers, t, n);
-    __syncthreads();
-    index = x.index;
-  }
-  return index;
+  return index < 0 ? lowest_unused(centers, t, x) : index;
+}
+
+// The draw of center t in a launch of its own.
+__global__ __launch_bounds__(kSeedThr) void kpp_draw_kernel(const float* __restrict__ D, const double* __restrict__ bsum,
+                                                           int nblk, int64_t n, double ut, int* __restrict__ centers,
+                                                           int t) {
+  __shared__ DrawLds x;
+  const int c = draw_center(D, bsum, nblk, n, ut, centers, t, x);
+  if (threadIdx.x == 0) centers[t] = c;
 }
 
 // Bound by latency and the read of the points (in the last-level cache up to
@@ -214,14 +235,15 @@ __device__ inline int draw_center(const float* __restrict__ D, const double* __r
 // in the pass (a launch per center instead of two) and four points' loads in
 // flight per group.
 //
-// Center t (c_first when t = 0, else drawn with ut from D_in and bsum_in):
+// Center t (c_first when t = 0, else drawn with ut from D_in and bsum_in, here or,
+// drawn set, before this launch):
 // D_out = min(D_in, distance), the nearest centers, the block's fp64 sum of
 // D_out (fixed order).  kd[i] = K(i,i) by the same routine (written when t =
 // 0).  V, when not null, receives each point's nearest center (the last pass).
 template <int KIND>
 __global__ __launch_bounds__(kSeedThr) void kpp_pass_kernel(const float* __restrict__ Xp, int64_t n, int d_pad,
                                                            KappaParams kp, int* __restrict__ centers, int t,
-                                                           int c_first, double ut, int nblk,
+                                                           int c_first, double ut, int nblk, bool drawn,
                                                            const float* __restrict__ D_in,
                                                            const double* __restrict__ bsum_in,
                                                            float* __restrict__ kd, float* __restrict__ D_out,
@@ -230,8 +252,8 @@ __global__ __launch_bounds__(kSeedThr) void kpp_pass_kernel(const float* __restr
   __shared__ DrawLds x;
   __shared__ float dpt[kSeedPts];
   const int tid = threadIdx.x, l = tid % kSeedLanes, p = tid / kSeedLanes;
-  const int c = t == 0 ? c_first : draw_center(D_in, bsum_in, nblk, n, ut, centers, t, x);
-  if (blockIdx.x == 0 && tid == 0) centers[t] = c;
+  const int c = t == 0 ? c_first : drawn ? centers[t] : draw_center(D_in, bsum_in, nblk, n, ut, centers, t, x);
+  if (!drawn && blockIdx.x == 0 && tid == 0) centers[t] = c;
   const int d4 = d_pad / 4;
   const int64_t i0 = (int64_t)blockIdx.x * kSeedPts + p * kSeedPer;
   const float *xi[kSeedPer], *xc[kSeedPer];
@@ -305,8 +327,14 @@ hipError_t launch_kpp_pass(const float* Xp, int64_t n, int d_pad, const KappaPar
                            int* bestc, double* bsum_out, int* V, hipStream_t s) {
   const int nblk = seed_blocks(n);
   const dim3 grid((unsigned)nblk), block(kSeedThr);
+  const bool drawn = t > 0 && nblk > kSeedFusedBlk;
+  if (drawn) {
+    hipLaunchKernelGGL(kpp_draw_kernel, dim3(1), block, 0, s, D_in, bsum_in, nblk, n, ut, centers, t);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
 #define KKM_KPP(KIND)                                                                                             \
-  hipLaunchKernelGGL(kpp_pass_kernel<KIND>, grid, block, 0, s, Xp, n, d_pad, kp, centers, t, c_first, ut, nblk, D_in, \
+  hipLaunchKernelGGL(kpp_pass_kernel<KIND>, grid, block, 0, s, Xp, n, d_pad, kp, centers, t, c_first, ut, nblk, drawn, D_in, \
                      bsum_in, kd, D_out, bestc, bsum_out, V)
   switch (kp.kind) {
     case LINEAR: KKM_KPP(LINEAR); break;

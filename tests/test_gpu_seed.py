@@ -187,3 +187,41 @@ def test_seed_full_size(oracle, cfg):
     same = validate_seed(oracle, kern, X, w.k, u, centers, V)
     assert it == 3 and np.all(np.diff(hist) <= 1e-5 * np.abs(hist[:-1]))
     print(f"[gpu] cfg {cfg}: centers {list(centers)} ({same} of {w.k - 1} draws equal), J {hist}", flush=True)
+
+
+@pytest.mark.parametrize("n", [102400, 102401, 150000])
+def test_draws_where_the_draw_gets_its_own_launch(n):
+    """Points of small integers: every distance and sum is exact, so the drawn
+    indices are those of the rule, on both sides of 1600 blocks of 64 points."""
+    k, d = 9, 4
+    rng = np.random.default_rng(n)
+    X = rng.integers(0, 6, (n, d)).astype(np.float32)
+    u = rng.random(k)
+    with Engine(X, "linear", mode="onthefly") as eng:
+        centers, V = eng.seed(k, u)
+    Z = X.astype(np.float64)
+    want, D = [int(u[0] * n)], None
+    ids = np.zeros(n, np.int32)
+    for t in range(k):
+        if t:
+            P = np.cumsum(D)
+            want.append(int(np.searchsorted(P, u[t] * P[-1], side="right")))
+        d2 = ((Z - Z[want[-1]]) ** 2).sum(1)
+        if t:
+            ids[d2 < D] = t
+        D = d2 if D is None else np.minimum(D, d2)
+    np.testing.assert_array_equal(centers, want)
+    np.testing.assert_array_equal(V, ids)
+
+
+@pytest.mark.parametrize("n,k", [(1500, 1000), (257, 257), (120000, 40)])
+def test_points_all_alike_take_the_lowest_indices(n, k):
+    """No distance is left after the first center: the lowest index not yet taken follows, k times."""
+    X = np.ones((n, 8), np.float32)
+    u = np.full(k, 0.01)
+    with Engine(X, "poly", 1.0, 1.0, 2, mode="onthefly") as eng:
+        centers, V = eng.seed(k, u)
+    first = int(0.01 * n)
+    rest = [i for i in range(k) if i != first][: k - 1]
+    np.testing.assert_array_equal(centers, [first] + rest)
+    assert not V.any()
