@@ -902,9 +902,9 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     c->nrm = c->Xp + (size_t)s.n_pad * s.d_pad;
     c->diagK = c->nrm + s.n_pad;
     c->bmax = c->diagK + s.n;
-    if ((rc = dalloc(c, &p, 64, c->build_allocs, "trace"))) return rc;
+    if ((rc = dalloc(c, &p, 256 + kStatWords * 4, c->build_allocs, "trace"))) return rc;
     c->trK = (double*)p;
-    c->maxnrm = (unsigned*)((char*)p + 8);
+    c->maxnrm = (unsigned*)((char*)p + 256);
     const bool stores_k = mode == KKM_MODE_RESIDENT || mode == KKM_MODE_PACKED;
     if (stores_k) {
       const size_t kb = k_bytes(c->wsz, mode, storage);
@@ -957,7 +957,8 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, kStatWords, c->stream); })))
     return rc;
   if ((rc = run(c, KKM_PHASE_STAGE, "stage", [&] {
-         return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, otf ? nullptr : c->Xf, c->xinv, c->stream);
+         return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, otf ? nullptr : c->Xf, c->xinv,
+                             c->Xf && kind != KKM_GAUSS, c->stream);
        })))
     return rc;
   c->fixups = -1;  // read from the device on demand

@@ -171,25 +171,26 @@ struct IterBufs {
   int small;
 };
 
-// What staging notes about the points, kStatWords words (zero on entry) from
-// the one the kernels are handed as maxnrm_bits on.
+// What staging notes about the points: kStatWords words (zero on entry) from the
+// one the kernels are handed as maxnrm_bits on, each used one in a cache line of
+// its own (every workgroup looks at it, the first ones raise it).
 enum {
-  kStatNorm,  // bits of the largest squared norm
-  // only with the split points' row factors:
-  kStatHigh,  // bits of the largest coordinate's absolute value, ...
-  kStatLow,   // ... complement of the bits of the smallest that is a nonzero row's largest
-  kStatLost,  // kLostAny: some row has a coordinate the split holds to less than 2^-22 of
-              // itself (below 2^-17 of the row's largest); kLostShare: a row has many (stage.hip)
-  kStatWords
+  kStatNorm = 0,  // bits of the largest squared norm
+  // only with the split points' row factors (kStatLost: where asked for):
+  kStatHigh = 32,  // bits of the largest coordinate's absolute value, its binade's end, ...
+  kStatLow = 64,   // ... complement of the bits of the smallest that is a nonzero row's largest, its binade's start
+  kStatLost = 96,  // kLostAny: some row has a coordinate the split holds to less than 2^-22 of
+                   // itself (below 2^-17 of the row's largest); kLostShare: a row has many (stage.hip)
+  kStatWords = 128
 };
 constexpr unsigned kLostAny = 1u, kLostShare = 2u;
 
 // ---------------------------------------------------------------- launchers
 // maxnrm_bits: kStatWords words, zero on entry.  xinv (may be null): also the
 // split points' row factors; Xf (may be null): also the split points (n_pad
-// rows), see split_mma.h
+// rows), see split_mma.h; ranges: also kStatLost
 hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
-                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, hipStream_t s);
+                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, bool ranges, hipStream_t s);
 // The split points (split_mma.h): rows a multiple of 32, nch = ceil(d_pad / 16).
 struct SplitPoints {
   const half_t* Xf;

@@ -22,8 +22,9 @@ namespace kkm {
 // scale in the split points (split_mma.h); Xf (may be null): those points in
 // operand order, zero past n.  The rows' largest coordinates come from the
 // same pass as the norms, and the second pass reads the staged rows back from
-// cache.  With xinv, stat also receives what split_runs asks about the rows'
-// ranges: a row has many coordinates that the split holds to fewer bits if they
+// cache.  With xinv, stat also receives the range of the rows' largest
+// coordinates, and with ranges (and xinv) what split_runs asks about each row's
+// own: a row has many coordinates that the split holds to fewer bits if they
 // are more than a sixteenth of its nonzero ones and at least three, or half.
 constexpr int kStageRows = 4;
 constexpr int kStageWaves = 4;
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
                                                                  float* __restrict__ nrm,
                                                                  unsigned* __restrict__ stat,
                                                                  half_t* __restrict__ Xf,
-                                                                 float* __restrict__ xinv) {
+                                                                 float* __restrict__ xinv, bool ranges) {
   __shared__ float wmax[kStageWaves], whigh[kStageWaves], wlow[kStageWaves];
   __shared__ int nnz[kStageBlk], nlost[kStageBlk];
   __shared__ float scl[kStageBlk];
@@ -93,19 +94,21 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
     wlow[w] = low;
   }
   __syncthreads();
+  // (a thread per word: one after the other their loads took 23 us more at
+  // 50000 points; the coordinates in whole binades, which few workgroups raise)
   if (threadIdx.x == 0) {
-    for (int q = 1; q < kStageWaves; ++q) {
-      m = fmaxf(m, wmax[q]);
-      high = fmaxf(high, whigh[q]);
-      low = fminf(low, wlow[q]);
-    }
+    for (int q = 1; q < kStageWaves; ++q) m = fmaxf(m, wmax[q]);
     raise_to(stat + kStatNorm, __float_as_uint(m));
-    if (xinv && high > 0.f) {
-      raise_to(stat + kStatHigh, __float_as_uint(high));
-      raise_to(stat + kStatLow, ~__float_as_uint(low));
-    }
+  } else if (threadIdx.x == 64 && xinv) {
+    high = whigh[0];
+    for (int q = 1; q < kStageWaves; ++q) high = fmaxf(high, whigh[q]);
+    if (high > 0.f) raise_to(stat + kStatHigh, __float_as_uint(high) | 0x7fffffu);
+  } else if (threadIdx.x == 128 && xinv) {
+    low = wlow[0];
+    for (int q = 1; q < kStageWaves; ++q) low = fminf(low, wlow[q]);
+    if (low < INFINITY) raise_to(stat + kStatLow, ~(__float_as_uint(low) & 0x7f800000u));
   }
-  if (!xinv) return;
+  if (!Xf && !ranges) return;
   const int nch = (d_pad + 15) / 16, l = lane & 31, h = lane >> 5;
   const float sc = scl[l];
   const float* row = Xp + (b0 + l) * d_pad + 8 * h;
@@ -117,13 +120,16 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
       v[0] = x0.x, v[1] = x0.y, v[2] = x0.z, v[3] = x0.w;
       v[4] = x1.x, v[5] = x1.y, v[6] = x1.z, v[7] = x1.w;
     }
+    if (ranges) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      nz += v[e] != 0.f ? 1 : 0;
-      lost += v[e] != 0.f && fabsf(v[e] * sc) < 0x1p-3f ? 1 : 0;
+      for (int e = 0; e < 8; ++e) {
+        nz += v[e] != 0.f ? 1 : 0;
+        lost += v[e] != 0.f && fabsf(v[e] * sc) < 0x1p-3f ? 1 : 0;
+      }
     }
     if (Xf) split_store(v, sc, Xf + split_unit(blockIdx.x, nch, c, 0) * kUnit + lane * 8);
   }
+  if (!ranges) return;
   atomicAdd(&nnz[l], nz);
   atomicAdd(&nlost[l], lost);
   __syncthreads();
@@ -139,11 +145,12 @@ __global__ __launch_bounds__(64 * kStageWaves) void stage_kernel(const float* __
 }
 
 hipError_t launch_stage(const float* X, int64_t n, int d, int d_pad, int64_t n_pad, float* Xp, float* nrm,
-                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, hipStream_t s) {
-  if (n_pad % kStageBlk || d_pad % 8 || (Xf && !xinv)) return hipErrorInvalidValue;
+                        unsigned* maxnrm_bits, half_t* Xf, float* xinv, bool ranges,
+                        hipStream_t s) {
+  if (n_pad % kStageBlk || d_pad % 8 || ((Xf || ranges) && !xinv)) return hipErrorInvalidValue;
   dim3 grid((unsigned)(n_pad / kStageBlk));
   hipLaunchKernelGGL(stage_kernel, grid, dim3(64 * kStageWaves), 0, s, X, n, d, d_pad, n_pad, Xp, nrm,
-                     maxnrm_bits, Xf, xinv);
+                     maxnrm_bits, Xf, xinv, ranges);
   return hipGetLastError();
 }
 

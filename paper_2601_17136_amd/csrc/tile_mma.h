@@ -230,11 +230,11 @@ __device__ inline bool gauss_needs_fix(float v, float nx, float ny, const KappaP
 // (kLostShare) is turned down whatever the other points are.  A few (points of
 // random coordinates have one in some 1e5) only matter to points much smaller
 // or larger than the row: with every row's largest coordinate within
-// kSplitRange of the others', the error they leave in K(x, y) is below 2^-27
+// kSplitRange of the others', the error they leave in K(x, y) is below 2^-26
 // |y|^2 per such coordinate.  The Gaussian's exponent is a difference against
 // the squared norms, where the same error is out of sight.
 constexpr float kSplitBlockErr = 5.0e-5f;
-constexpr float kSplitRange = 4096.f;
+constexpr float kSplitRange = 8192.f;
 template <int KIND, bool PANEL>
 __device__ inline bool split_runs(const unsigned* maxnrm_bits, const KappaParams& kp) {
   const float m = __uint_as_float(*maxnrm_bits);
