@@ -111,8 +111,14 @@ __global__ __launch_bounds__(256, 2) void onthefly_split_kernel(
     rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm_s[row0 + tid] : 0.f;
   }
   if constexpr (kNarrow) {
-    const float4* src = (const float4*)(Xf + split_unit(row0 / 32, NCH, 0, 0) * kUnit);
-    for (int f = tid; f < 4 * NCH * 2 * 64; f += 256) ((float4*)lds)[f] = src[f];
+    // the rows of the chunks from the turn on go to LDS negated (split_turn)
+    const uint4* src = (const uint4*)(Xf + split_unit(row0 / 32, NCH, 0, 0) * kUnit);
+    for (int f = tid; f < 4 * NCH * 2 * 64; f += 256) {
+      const unsigned neg = f / 128 % NCH >= split_turn(NCH) ? 0x80008000u : 0u;
+      uint4 x = src[f];
+      x.x ^= neg, x.y ^= neg, x.z ^= neg, x.w ^= neg;
+      ((uint4*)lds)[f] = x;
+    }
   }
   __syncthreads();
   const bool fix = KIND == GAUSS && gauss_needs_fix(1.f, maxnrm, maxnrm, kp);
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(256, 2) void onthefly_split_kernel(
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
+          for (int r = 0; r < 16; ++r) acc[bi][bj][r] = split_turn(NCH) ? 0.f : -0.f;
       const half_t* bs = Xf + split_unit(col0 / 32 + wn * 2, NCH, 0, 0) * kUnit + lane * 8;
       const char* as = lds + (wm * 2 * NCH * 2) * 1024 + lane * 16;
       half8 b[2][2][2];
@@ -248,11 +254,8 @@ __global__ __launch_bounds__(256, 2) void onthefly_split_kernel(
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-          for (int p = 0; p < 2; ++p) {
-            a[bi][p] = *(const half8*)(as + ((bi * NCH + c) * 2 + p) * 1024);
-            if (c >= split_turn(NCH)) a[bi][p] = -a[bi][p];
-          }
-        if (c == split_turn(NCH)) split_negate(acc);
+          for (int p = 0; p < 2; ++p) a[bi][p] = *(const half8*)(as + ((bi * NCH + c) * 2 + p) * 1024);
+        if (c > 0 && c == split_turn(NCH)) split_negate(acc);
         split_mfma(a, b[c & 1], acc);
         __builtin_amdgcn_sched_barrier(0);  // operands are read one chunk ahead, not further (registers)
       }

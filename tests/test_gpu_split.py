@@ -387,3 +387,18 @@ def test_on_the_fly_bits_do_not_depend_on_seeding(spare):
         after = eng.step(cl, k)
     for key in ("E", "D", "z", "cl"):
         assert np.array_equal(first[key], again[key]) and np.array_equal(first[key], after[key]), key
+
+
+@pytest.mark.parametrize("d", [33, 54, 100, 128, 301])
+def test_entries_have_no_bias(d):
+    """Sums of K over a cluster, and the objective, see the mean error of its
+    entries.  Roundings of random sign leave next to nothing of it over 4
+    million entries (the rows' own, 2^-25 over sqrt(d) and over sqrt(2000) rows,
+    2^-33 at most); a turn of the sum's sign at the wrong chunk leaves 2e-9."""
+    _torch_cuda()
+    X = np.random.default_rng(d).random((2000, d), dtype=np.float32)
+    with Engine(X, "linear", mode="packed") as eng:
+        K = eng.K_rows().astype(np.float64)
+    ref = X.astype(np.float64) @ X.astype(np.float64).T
+    off = ~np.eye(len(X), dtype=bool)
+    assert abs((K - ref)[off].sum() / ref[off].sum()) <= 2.0 ** -30
