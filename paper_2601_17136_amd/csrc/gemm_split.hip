@@ -7,10 +7,11 @@
 //
 // Tiles, layouts and epilogue are those of gemm_kappa.hip: the upper block
 // triangle of 128 x 128 tiles (I <= J), an entry's accumulator register and
-// lane as there (both matrix instructions hold a 32 x 32 block alike).  A
-// diagonal tile's entries (i, j) and (j, i) would add hi lo and lo hi in
-// different orders, so the one with i <= j is stored in both places and K
-// stays exactly symmetric.
+// lane as there (both matrix instructions hold a 32 x 32 block alike).  Entries
+// (i, j) and (j, i) would add hi lo and lo hi in different orders: on a diagonal
+// tile the one with i <= j is stored in both places, and a panel's tiles below
+// the diagonal add them in the other order (split_mfma).  So K is exactly
+// symmetric, and a panel or block holds the bits of the full K.
 #include "split_mma.h"
 
 #include <algorithm>
@@ -40,10 +41,14 @@ struct BuildOut {
 
 // Lists the Gaussian entries marked in mk (bit 31 - 2r - bj of mk[bi]: entry r
 // of the 32 x 32 block (bi, bj)) for recomputation: the square layouts each
-// pair once (i < j), a panel every entry it stores off the diagonal.  A scan of
-// the lanes' counts and one atomic per wavefront give the slots.
+// pair once (i < j), a panel every entry it stores off the diagonal (on a
+// diagonal tile (i, j) and (j, i) as (i, j), i < j, is marked).  A scan of the
+// lanes' counts and one atomic per wavefront give the slots.
 template <typename KT, bool PANEL>
-__device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, bool inside, const BuildOut<KT>& o) {
+__device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, bool diagonal, bool inside,
+                                   const BuildOut<KT>& o) {
+  const bool both = PANEL && diagonal;
+  auto stored = [&](int64_t gi, int64_t gj) { return gi < o.r1 && gj < o.c1; };
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int seg = (int)(blockIdx.x % kFixSegs);
   auto entry = [&](int bi, int bit, int64_t& gi, int64_t& gj) {
@@ -58,9 +63,10 @@ __device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, 
       for (unsigned m = mk[bi]; m; m &= m - 1u) {
         int64_t gi, gj;
         entry(bi, __ffs(m) - 1, gi, gj);
-        if (!(PANEL ? gi != gj && gi < o.r1 && gj < o.c1 : gi < gj && gj < o.n)) mk[bi] &= ~(m & -m);
+        if (!(both ? gi < gj : PANEL ? stored(gi, gj) : gi < gj && gj < o.n)) mk[bi] &= ~(m & -m);
+        else if (both) cnt += (stored(gi, gj) ? 1u : 0u) + (stored(gj, gi) ? 1u : 0u);
       }
-    cnt += (unsigned)__popc(mk[bi]);
+    if (!both) cnt += (unsigned)__popc(mk[bi]);
   }
   unsigned pre = cnt;  // inclusive scan over the lanes
 #pragma unroll
@@ -77,9 +83,13 @@ __device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, 
     for (unsigned m = mk[bi]; m; m &= m - 1u) {
       int64_t gi, gj;
       entry(bi, __ffs(m) - 1, gi, gj);
-      if (base < (unsigned long long)o.seg_cap)
-        o.fix_list[(int64_t)seg * o.seg_cap + (int64_t)base] = make_int2((int)gi, (int)gj);
-      ++base;
+      auto put = [&](int64_t i, int64_t j) {
+        if (base < (unsigned long long)o.seg_cap)
+          o.fix_list[(int64_t)seg * o.seg_cap + (int64_t)base] = make_int2((int)i, (int)j);
+        ++base;
+      };
+      if (!both || stored(gi, gj)) put(gi, gj);
+      if (both && stored(gj, gi)) put(gj, gi);
     }
 }
 
@@ -133,7 +143,7 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi) any |= mk[bi];
     if (__ballot(any != 0u))
-      list_fixups<KT, PANEL>(mk, gi0, gj0,
+      list_fixups<KT, PANEL>(mk, gi0, gj0, I == J,
                                  I != J && (PANEL ? gi0 + 64 <= o.r1 && gj0 + 64 <= o.c1 : gj0 + 64 <= o.n), o);
   }
 
@@ -157,8 +167,8 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
     cend = o.ld;
   }
   if (I == J) {
-    // a diagonal tile: diag K, and (square layouts) each pair from its entry
-    // with i <= j, stored in both places
+    // a diagonal tile: diag K, and each pair from its entry with i <= j, stored
+    // in both places
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
@@ -171,13 +181,19 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
           // exp(0), or kappa of the squared norm: a square's lo lo, which the
           // product leaves out, is never negative, so tr K would come out low (2^-25 of it)
           if (gi == gj) v = KIND == GAUSS ? 1.f : kappa<KIND>(rcn[il], 0.f, 0.f, kp);
+          if (gi > gj) continue;
+          if (PANEL) {
+            if (gi == gj && gi < rlim && gj < clim) o.diagK[gi] = v;
+            if (gi < rlim && gj < cend) Kb[il * S + jl] = (KT)(gj < clim ? v : 0.f);
+            if (gi < gj && gj < rlim && gi < cend) Kb[(gj - gi0) * S + (gi - gj0)] = (KT)(gi < clim ? v : 0.f);
+            continue;
+          }
           if (gi >= rlim || gj >= cend) continue;
           if (gi == gj && gj < clim) o.diagK[gi] = v;
-          if (!PANEL && gi > gj) continue;
           if (gj >= clim) v = 0.f;
           const float wi = kHalf && o.kw ? 1.f / o.kw[gi] : 1.f;
           Kb[il * S + jl] = (KT)(v * wi);
-          if (!PANEL && gi < gj && gj < clim) {
+          if (gi < gj && gj < clim) {
             const float wj = kHalf && o.kw ? 1.f / o.kw[gj] : 1.f;
             Kb[(gj - gi0) * S + (gi - gj0)] = (KT)(v * wj);
           }
@@ -358,10 +374,12 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   }
 
   floatx16 acc[2][2];
-  split_tile(Xf, nch, row0 / 32, col0 / 32, lds, wave, lane, acc);  // ends with a barrier: the buffers become LDS tiles
-
   const int64_t gi0 = row0 + wm * 64, gj0 = col0 + wn * 64;
-  if (gi0 >= (PANEL ? o.r1 : o.n) || (!PANEL && gi0 > gj0 + 63)) return;  // nothing stored
+  // ends with a barrier: the buffers become LDS tiles
+  if (PANEL && I > J) split_tile<true>(Xf, nch, row0 / 32, col0 / 32, lds, wave, lane, acc);
+  else split_tile(Xf, nch, row0 / 32, col0 / 32, lds, wave, lane, acc);
+
+  if (gi0 >= (PANEL ? o.r1 : o.n) || (I == J && gi0 > gj0)) return;  // nothing stored
   const bool est = KIND == GAUSS && (bmax ? gauss_needs_fix(1.f, bmax[I], bmax[J], kp)
                                           : gauss_needs_fix(1.f, maxnrm, maxnrm, kp));
   build_epilogue<KIND, KT, PANEL>(acc, rinv + wm * 64, rcn + wm * 64, cf, cnj, I, J, gi0, gj0, est,

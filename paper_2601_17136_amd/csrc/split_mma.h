@@ -70,7 +70,9 @@ __device__ inline void split_store(const float (&v)[8], float sc, half_t* u) {
   *(half8*)(u + kUnit) = lo;
 }
 
-// acc += A B^T of one chunk, for 2 x 2 blocks of 32 x 32 (hi in part 0).
+// acc += A B^T of one chunk, for 2 x 2 blocks of 32 x 32 (hi in part 0).  SWAP:
+// lo hi before hi lo, so that entry (j, i) adds the products in (i, j)'s order.
+template <bool SWAP = false>
 __device__ inline void split_mfma(const half8 (&a)[2][2], const half8 (&b)[2][2], floatx16 (&acc)[2][2]) {
   // a block's three products are four instructions apart, so none waits for
   // the one before it
@@ -80,7 +82,7 @@ __device__ inline void split_mfma(const half8 (&a)[2][2], const half8 (&b)[2][2]
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj)
-        acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p == 2], b[bj][p == 1], acc[bi][bj], 0, 0, 0);
+        acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p == (SWAP ? 1 : 2)], b[bj][p == (SWAP ? 2 : 1)], acc[bi][bj], 0, 0, 0);
 }
 
 typedef __attribute__((address_space(1))) const void gvoid;
@@ -94,6 +96,7 @@ constexpr int kSplitLds = 2 * 16 * 1024;  // split_tile's LDS: two chunks of 16 
 // and 4 column blocks, hi and lo) go from global memory straight to LDS, double
 // buffered: chunk c + 1 is requested once chunk c's operands are in registers
 // and arrives during its products; one barrier per chunk and one at the end.
+template <bool SWAP = false>
 __device__ inline void split_tile(const half_t* __restrict__ Xf, int nch, int64_t rb, int64_t cb, char* lds, int wave,
                                   int lane, floatx16 (&acc)[2][2]) {
   constexpr int kPer = 4;  // units per wavefront: unit u = 4 wave + v is part u % 2 of block u / 2
@@ -141,7 +144,7 @@ __device__ inline void split_tile(const half_t* __restrict__ Xf, int nch, int64_
 #pragma unroll
         for (int p = 0; p < 2; ++p) a[bi][p] = -a[bi][p];
     }
-    split_mfma(a, b, acc);
+    split_mfma<SWAP>(a, b, acc);
   };
   const int turn = split_turn(nch);
   int c = 0;

@@ -402,3 +402,37 @@ def test_entries_have_no_bias(d):
     ref = X.astype(np.float64) @ X.astype(np.float64).T
     off = ~np.eye(len(X), dtype=bool)
     assert abs((K - ref)[off].sum() / ref[off].sum()) <= 2.0 ** -30
+
+
+@pytest.mark.parametrize("kind", ["linear", "poly", "gauss"])
+@pytest.mark.parametrize("n,d", [(1000, 70), (897, 33)])
+def test_blocks_hold_the_bits_of_the_full_k(n, d, kind):
+    """Entry (i, j) of any block is entry (i, j) of the full K, bit for bit, above,
+    on and below the diagonal, ragged ends of rows and columns included; the
+    Gaussian with many entries recomputed."""
+    torch = _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    rng = np.random.default_rng(n)
+    X = (rng.standard_normal((9, d))[rng.integers(0, 9, n)] + 0.05 * rng.standard_normal((n, d))).astype(np.float32)
+    g, c, p = {"linear": (1.0, 0.0, 1), "poly": (0.5, 1.0, 3), "gauss": (20.0 / d, 0.0, 1)}[kind]
+    with Engine(X, kind, g, c, p, mode="resident") as eng:
+        K = eng.K_rows()
+        assert kind != "gauss" or eng.info()["fixups"] > n
+    assert np.array_equal(K, K.T)
+    Xd = torch.from_numpy(X).cuda()
+    ctx = kkm.kkm_create(kkm.current_stream_handle())
+    try:
+        for r0, r1, c0, c1 in [(0, n, 0, n), (128, n, 0, 700), (0, 300, 256, n), (256, 700, 128, 650), (640, n, 640, n),
+                               (384, 400, 384, 500), (384, 500, 384, 400), (128, 129, 128, 129)]:
+            kkm.kkm_build_block(ctx, Xd, n, d, kkm.KINDS[kind], kkm.make_params(g, c, p), r0, r1, c0, c1)
+            out = torch.empty((r1 - r0, c1 - c0), device="cuda")
+            kkm.kkm_copy_kernel_rows(ctx, r0, r1, out)
+            assert np.array_equal(out.cpu().numpy(), K[r0:r1, c0:c1]), (r0, r1, c0, c1)
+            # the columns past the block's end are zero: sums over them too
+            E = torch.empty((c1 - c0, 1), device="cuda")
+            kkm.kkm_block_spmm(ctx, torch.zeros(r1 - r0, dtype=torch.int32, device="cuda"), 1, E)
+            ref = K[r0:r1, c0:c1].astype(np.float64).sum(0)
+            scale = np.abs(K[r0:r1, c0:c1]).astype(np.float64).sum(0)
+            assert np.all(np.abs(E.cpu().numpy()[:, 0] - ref) <= 2.0 ** -24 * (r1 - r0 + 2) * scale)
+    finally:
+        kkm.kkm_destroy(ctx)
