@@ -243,8 +243,10 @@ int hip_fail(kkm_ctx* c, hipError_t e, const char* what) {
 
 // Every buffer is plain hipMalloc memory.  Physically contiguous allocations
 // (hipDeviceMallocContiguous) for a K of 4 GB and more measured 0-1.5% faster
-// per update, but memory allocated after such a buffer had been freed held
-// stale lines in some XCDs' L2: a K build on it came out wrong in places.
+// per update on K of 7-29 GB and 6% on one of 80 GB (n = 200000: 13.4 against
+// 14.3 ms), but a K build on memory allocated after such a buffer of 40 GB had
+// been freed came out wrong in places (128-byte lines of the points, on two
+// XCDs), so none are made.
 void release(kkm_ctx* c, std::vector<Alloc>& owner) {
   for (const Alloc& a : owner) {
     (void)hipFree(a.p);

@@ -1,5 +1,4 @@
-"""A large K (8.5 GB, allocated as contiguous memory) within a budget of
-exactly what kkm_plan asks for, and with the default budget.  kkm_plan counts
+"""A large K (8.5 GB) within a budget of exactly what kkm_plan asks for, and with the default budget.  kkm_plan counts
 K, the staged points and the iteration scratch; the Gaussian build's fix-up
 list uses spare room while building and gives it up to the first update's
 scratch when the budget has no room for both.  Both contexts must stay within
