@@ -30,7 +30,10 @@ constexpr int kChunk = 1024;
 // coordinates; the fp32 product's, one rounding per 2.  Measured over random
 // signs, image-like points and blobs, all kernels: 0.66-0.95 of the fp32
 // product's error at d = 32 .. 64 and less beyond, 0.91-1.03 at 24, 1.0-1.35
-// at 16 and 17, up to 1.8 at 6.
+// at 16 and 17, up to 1.8 at 6.  Error of E, a sum over a cluster rounded to
+// fp32: 0.93-1.01 at 25 .. 64 and 0.45-0.96 at 784 on image-like points,
+// 1.03-1.13 and 0.86-1.0 on blobs and standardised points, 1.22 at 25, 1.16 at 64,
+// 1.09 at 128, 0.89 at 301 on rings, whose two large coordinates alone round.
 constexpr int kSplitMinDpad = 32;
 
 // The sweep kernels of small widths take d_pad up to this.
