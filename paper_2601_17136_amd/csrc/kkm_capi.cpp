@@ -904,9 +904,9 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     c->nrm = c->Xp + (size_t)s.n_pad * s.d_pad;
     c->diagK = c->nrm + s.n_pad;
     c->bmax = c->diagK + s.n;
-    if ((rc = dalloc(c, &p, 256 + kStatWords * 4, c->build_allocs, "trace"))) return rc;
+    if ((rc = dalloc(c, &p, 8 + kStatWords * 4, c->build_allocs, "trace"))) return rc;
     c->trK = (double*)p;
-    c->maxnrm = (unsigned*)((char*)p + 256);
+    c->maxnrm = (unsigned*)((char*)p + 8);
     const bool stores_k = mode == KKM_MODE_RESIDENT || mode == KKM_MODE_PACKED;
     if (stores_k) {
       const size_t kb = k_bytes(c->wsz, mode, storage);

@@ -175,16 +175,17 @@ struct IterBufs {
 };
 
 // What staging notes about the points: kStatWords words (zero on entry) from the
-// one the kernels are handed as maxnrm_bits on, each used one in a cache line of
-// its own (every workgroup looks at it, the first ones raise it).
+// one the kernels are handed as maxnrm_bits on.  Every workgroup looks at the
+// used ones and the first ones raise them, so the two raised most lie 128 bytes
+// apart; with 8 bytes before them they fill 256.
 enum {
   kStatNorm = 0,  // bits of the largest squared norm
   // only with the split points' row factors (kStatLost: where asked for):
   kStatHigh = 32,  // bits of the largest coordinate's absolute value, its binade's end, ...
-  kStatLow = 64,   // ... complement of the bits of the smallest that is a nonzero row's largest, its binade's start
-  kStatLost = 96,  // kLostAny: some row has a coordinate the split holds to less than 2^-22 of
+  kStatLow = 48,   // ... complement of the bits of the smallest that is a nonzero row's largest, its binade's start
+  kStatLost = 16,  // kLostAny: some row has a coordinate the split holds to less than 2^-22 of
                    // itself (below 2^-17 of the row's largest); kLostShare: a row has many (stage.hip)
-  kStatWords = 128
+  kStatWords = 49
 };
 constexpr unsigned kLostAny = 1u, kLostShare = 2u;
 

@@ -56,3 +56,16 @@ def test_large_k_within_the_planned_budget(oracle):
         assert np.array_equal(a[key], b[key]), key
     assert a["J"] == b["J"]
     assert int(a["counts"].sum()) == N
+
+
+def test_the_plan_holds_the_history_of_a_few_hundred_updates():
+    """kkm_plan's bytes, to the byte, build a small problem and run 277 updates of it (12 bytes of history each)."""
+    torch = pytest.importorskip("torch")
+    assert torch.cuda.is_available()
+    from paper_2601_17136_amd import kkm
+    X = datagen.make_points(2, n=300, d=40)[0]
+    for mode in ("packed", "resident", "onthefly"):
+        _, need = kkm.kkm_plan(300, 40, 4, kkm.KKM_LINEAR, 1 << 40, kkm.MODES[mode])
+        with Engine(X, "linear", mode=mode, mem_budget=need, k_hint=4) as eng:
+            _, it, hist = eng.iterate(datagen.random_init(300, 4, 1), 4, 277)
+            assert it == 277 and np.all(np.isfinite(hist)) and eng.info()["bytes_total"] <= need
