@@ -95,12 +95,15 @@ __device__ inline void list_fixups(unsigned (&mk)[2], int64_t gi0, int64_t gj0, 
 
 // One wavefront's part of tile (I, J): rows gi0 .. gi0 + 63, columns gj0 ..
 // gj0 + 63.  rinv, rcn: the rows' -1/s and c|x|^2 (Gaussian) or |x|^2, in LDS;
+// rw, cw: for binary16 storage, 1/kw of the rows and columns, in LDS (a load and
+// a division per stored row took 20 us of a small build);
 // cf, cnj: the columns' factor (col_factor) and c|x|^2.  est:
 // Gaussian entries of the tile may need the fix-up.  Tw: 32 x 65 floats of LDS
 // of the wavefront's own (mirror tiles and binary16 storage), ordered within
 // the wavefront.
 template <int KIND, typename KT, bool PANEL>
-__device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, const float* rcn,
+__device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, const float* rcn, const float* rw,
+                                      const float* cw,
                                       const float (&cf)[2], const float (&cnj)[2], int64_t I, int64_t J,
                                       int64_t gi0, int64_t gj0, bool est, float* Tw, const KappaParams& kp,
                                       const BuildOut<KT>& o) {
@@ -191,10 +194,10 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
           if (gi >= rlim || gj >= cend) continue;
           if (gi == gj && gj < clim) o.diagK[gi] = v;
           if (gj >= clim) v = 0.f;
-          const float wi = kHalf && o.kw ? 1.f / o.kw[gi] : 1.f;
+          const float wi = kHalf ? rw[il] : 1.f;
           Kb[il * S + jl] = (KT)(v * wi);
           if (gi < gj && gj < clim) {
-            const float wj = kHalf && o.kw ? 1.f / o.kw[gj] : 1.f;
+            const float wj = kHalf ? cw[jl] : 1.f;
             Kb[(gj - gi0) * S + (gi - gj0)] = (KT)(v * wj);
           }
         }
@@ -242,11 +245,17 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
       const int64_t gj = gj0 + lane;
       const int nrows = (int)min<int64_t>(32, rlim - (gi0 + bi * 32));
       KT* dst = Kb + (int64_t)(bi * 32) * S + lane;
-      if (gj < cend)
-        for (int rr = 0; rr < nrows; ++rr) {
-          const float inv = o.kw ? 1.f / o.kw[gi0 + bi * 32 + rr] : 1.f;
-          __builtin_nontemporal_store((KT)((gj < clim ? Tw[rr * 65 + lane] : 0.f) * inv), dst + rr * S);
+      auto put = [&](int rr) {
+        __builtin_nontemporal_store((KT)((gj < clim ? Tw[rr * 65 + lane] : 0.f) * rw[bi * 32 + rr]), dst + rr * S);
+      };
+      if (gj < cend) {
+        if (nrows >= 32) {
+#pragma unroll
+          for (int rr = 0; rr < 32; ++rr) put(rr);
+        } else {
+          for (int rr = 0; rr < nrows; ++rr) put(rr);
         }
+      }
       ordered();
     }
   }
@@ -264,7 +273,7 @@ __device__ inline void build_epilogue(floatx16 (&acc)[2][2], const float* rinv, 
       KT* dst = o.K + gj1 * o.ld + gi;
       auto put = [&](int rr) {
         const float v = Tw[rr * 65 + lane];
-        __builtin_nontemporal_store((KT)(kHalf && o.kw ? v * (1.f / o.kw[gj1 + rr]) : v), dst + rr * o.ld);
+        __builtin_nontemporal_store((KT)(kHalf ? v * cw[bj * 32 + rr] : v), dst + rr * o.ld);
       };
       if (nrows >= 32) {
 #pragma unroll
@@ -342,6 +351,7 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   constexpr int kTBytes = 4 * 32 * 65 * 4;
   __shared__ __attribute__((aligned(1024))) char lds[kSplitLds > kTBytes ? kSplitLds : kTBytes];
   __shared__ __attribute__((aligned(16))) float rinv[kTile], rcn[kTile];
+  __shared__ float rw[sizeof(KT) == 2 ? kTile : 1], cw[sizeof(KT) == 2 ? kTile : 1];
   const float maxnrm = __uint_as_float(*maxnrm_bits);
   if (!split_runs<KIND, PANEL>(maxnrm_bits, kp)) return;  // gemm_kappa_kernel builds K then (uniform)
 
@@ -365,6 +375,10 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
     rinv[tid] = -xinv[row0 + tid];  // the product comes negated
     rcn[tid] = KIND == GAUSS ? kp.neg_g_log2e * nrm[row0 + tid] : nrm[row0 + tid];
   }
+  if (sizeof(KT) == 2 && tid < kTile) {  // (a row past n is not stored)
+    rw[tid] = o.kw && row0 + tid < o.n ? 1.f / o.kw[row0 + tid] : 1.f;
+    cw[tid] = o.kw && col0 + tid < o.n ? 1.f / o.kw[col0 + tid] : 1.f;
+  }
   float cf[2], cnj[2] = {0.f, 0.f};
 #pragma unroll
   for (int bj = 0; bj < 2; ++bj) {
@@ -382,7 +396,8 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(
   if (gi0 >= (PANEL ? o.r1 : o.n) || (I == J && gi0 > gj0)) return;  // nothing stored
   const bool est = KIND == GAUSS && (bmax ? gauss_needs_fix(1.f, bmax[I], bmax[J], kp)
                                           : gauss_needs_fix(1.f, maxnrm, maxnrm, kp));
-  build_epilogue<KIND, KT, PANEL>(acc, rinv + wm * 64, rcn + wm * 64, cf, cnj, I, J, gi0, gj0, est,
+  build_epilogue<KIND, KT, PANEL>(acc, rinv + wm * 64, rcn + wm * 64, rw + wm * 64, cw + wn * 64, cf, cnj, I, J, gi0,
+                                      gj0, est,
                                       (float*)lds + wave * (32 * 65), kp, o);
 }
 
