@@ -27,7 +27,7 @@ namespace kkm {
 // own: a row has many coordinates that the split holds to fewer bits if they
 // are more than a sixteenth of its nonzero ones and at least three, or half.
 constexpr int kStageRows = 4;
-constexpr int kStageWaves = 4;
+constexpr int kStageWaves = 8;  // (a block's rows at once: two turns of 4 wavefronts took a small build 2-4 us longer)
 constexpr int kStageBlk = 32;
 
 __device__ inline void raise_to(unsigned* word, unsigned bits) {
