@@ -314,7 +314,7 @@ __global__ __launch_bounds__(256, 2) void onthefly_kernel(
   floatx16 acc[2][2];
   for (int J = jt0; J < jt1; ++J) {
     const int64_t col0 = (int64_t)J * kTile;
-    mma_tile(Xs + row0 * d_pad, Xs + col0 * d_pad, d_pad, lds, acc);
+    mma_tile(Xs + row0 * d_pad, Xs + col0 * d_pad, d_pad, lds, acc, threadIdx.x);
     kappa_tile<KIND, FIX>(acc, Xs, nrm_s, rn, n, d_pad, row0, col0, kp);
     const int64_t last = (col0 + kTile - 1 < n) ? col0 + kTile - 1 : n - 1;
     const int cf = cs[col0], cl_last = cs[last];
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(256, 2) void kernel_rows_kernel(const float* __rest
   float* const rn = lds + kLdsFloats;
   if (threadIdx.x < kTile) rn[threadIdx.x] = (KIND == GAUSS ? kp.neg_g_log2e : 1.f) * nrm[row0 + threadIdx.x];
   floatx16 acc[2][2];
-  mma_tile(Xp + row0 * d_pad, Xp + col0 * d_pad, d_pad, lds, acc);
+  mma_tile(Xp + row0 * d_pad, Xp + col0 * d_pad, d_pad, lds, acc, threadIdx.x);
   if (any_fix(maxnrm_bits, kp)) kappa_tile<KIND, true>(acc, Xp, nrm, rn, n, d_pad, row0, col0, kp);
   else kappa_tile<KIND, false>(acc, Xp, nrm, rn, n, d_pad, row0, col0, kp);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -25,8 +25,8 @@ constexpr int kLdsFloats = 2 * kLdsBuf;     // double-buffered: 40 KB
 // nor multiplied (h takes k = 4h .. 4h+3, four steps), so a row pays for at
 // most 7 zero columns.
 __device__ inline void mma_tile(const float* __restrict__ Xa, const float* __restrict__ Xb,
-                                int d_pad, float* lds, floatx16 acc[2][2]) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                int d_pad, float* lds, floatx16 acc[2][2], int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int l32 = lane & 31, h = lane >> 5;
   const int f0 = tid, f1 = tid + 256;
