@@ -956,7 +956,11 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
     }
   }
   const SplitPoints sp{c->Xf, c->xinv, s.n_pad, (s.d_pad + 15) / 16};
-  if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] { return launch_zero_ints((int*)c->maxnrm, kStatWords, c->stream); })))
+  // staging's words and the fix-up list's counts
+  if ((rc = run(c, KKM_PHASE_STAGE, "zero", [&] {
+         return launch_zero_ints((int*)c->maxnrm, kStatWords, c->stream, (int*)c->fix_count,
+                                 c->fix_count ? 2 * kFixSegs : 0);
+       })))
     return rc;
   if ((rc = run(c, KKM_PHASE_STAGE, "stage", [&] {
          return launch_stage(X, n, d, s.d_pad, s.n_pad, c->Xp, c->nrm, c->maxnrm, otf ? nullptr : c->Xf, c->xinv,
@@ -964,10 +968,6 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
        })))
     return rc;
   c->fixups = -1;  // read from the device on demand
-  if (c->fix_count && (rc = run(c, KKM_PHASE_FIXUP, "zero", [&] {
-        return launch_zero_ints((int*)c->fix_count, 2 * kFixSegs, c->stream);
-      })))
-    return rc;
   c->built = true;  // buffers exist from here on; free_build releases them
 
   if (mode == KKM_MODE_ONTHEFLY) {

@@ -277,7 +277,7 @@ hipError_t launch_kpp_pass(const float* Xp, int64_t n, int d_pad, const KappaPar
                            int* bestc, double* bsum_out, int* V, hipStream_t s);
 hipError_t launch_fill_diag(float* diagK, int64_t n, float v, hipStream_t s);
 
-hipError_t launch_zero_ints(int* p, int64_t count, hipStream_t s);
+hipError_t launch_zero_ints(int* p, int64_t count, hipStream_t s, int* q = nullptr, int64_t qcount = 0);
 // mode 0: validate cl_in, count, per-block histogram (no distances).
 // mode 1: distances from Et/zpart/counts_in, argmin -> cl_out, new counts.
 // counts_out must be zero on entry (scatter clears the next update's).

@@ -196,16 +196,17 @@ hipError_t launch_fill_diag(float* diagK, int64_t n, float v, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void zero_ints_kernel(int* __restrict__ p, int64_t count) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void zero_ints_kernel(int* __restrict__ p, int64_t count, int* __restrict__ q, int64_t qcount) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) p[i] = 0;
+  if (i < qcount) q[i] = 0;
 }
 
 // A fill kernel rather than hipMemsetAsync, so a captured graph replays it safely.
-hipError_t launch_zero_ints(int* p, int64_t count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_ints_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, p,
-                     count);
+hipError_t launch_zero_ints(int* p, int64_t count, hipStream_t s, int* q, int64_t qcount) {
+  const int64_t most = std::max(count, qcount);
+  if (most <= 0) return hipSuccess;
+  hipLaunchKernelGGL(zero_ints_kernel, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, s, p, count, q, qcount);
   return hipGetLastError();
 }
 
