@@ -222,8 +222,11 @@ int kkm_check_iterate_args(int64_t n, int32_t k, int32_t max_iter);
  * ONTHEFLY: stages X and row norms only.
  * storage F16 (RESIDENT, PACKED): K in binary16 with row scales, see
  *   kkm_storage; diag K stays fp32.
- * From 25 features up the products of the build and of the on-the-fly update
- *   run on the binary16 matrix cores, each coordinate as two binary16 parts with
+ * From 25 features up, and not for few points of few features (for up to 128
+ *   features beyond 2048 points or with binary16 storage; Gaussian K beyond 4096,
+ *   of 129 to 256 features beyond 2048; panels and blocks of up to 64 features
+ *   beyond 4096, on the fly beyond 1024), the products of the build and of the
+ *   on-the-fly update run on the binary16 matrix cores, each coordinate as two binary16 parts with
  *   fp32 sums, where the budget has room for the split points beside what
  *   kkm_plan counts (4 bytes per padded coordinate and 4 to 8 per point; on the
  *   fly also the seeding scratch); else, and for points whose range or norms

@@ -938,7 +938,7 @@ int build_impl(kkm_ctx* c, const float* X, int64_t n, int32_t d, int32_t kind, c
   // and, on the fly, where every update takes them, the seeding scratch too.
   const bool f16 = storage == KKM_STORE_F16;
   const bool otf = mode == KKM_MODE_ONTHEFLY;
-  if (s.d_pad >= kSplitMinDpad && !c->Xf) {
+  if (!c->Xf && split_wanted(n, s.d_pad, kind == KKM_GAUSS, f16, otf, panel)) {
     const size_t split = split_bytes(s.n_pad, s.d_pad), bytes = split + (otf ? (size_t)s.n_pad * 4 : 0);
     const int32_t kh = std::min<int64_t>(params->k_hint, n);
     const size_t scratch = c->ws_allocs.empty() ? ws_bytes(c->wsz, kh > 0 ? kh : 1, mode) + 4096 : 0;

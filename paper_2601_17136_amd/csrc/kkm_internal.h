@@ -39,6 +39,32 @@ constexpr int kSplitMinDpad = 32;
 // The sweep kernels of small widths take d_pad up to this.
 constexpr int kRegMaxDpad = 64;
 
+// Whether a build or sweep of this size takes the split points at all.  Small
+// problems are bound by launches, and the fp32 kernels need one fewer and no
+// split points.  A build call, microseconds, fp32 / split: linear packed, d = 25
+// 35 / 37 at n = 500, 37 / 39 at 2000, 42 / 41 at 3000, 65 / 55 at 6500; d = 66
+// 36 / 39, 38 / 41, 44 / 43, 76 / 62; d = 128 40 / 40, 43 / 43, 52 / 46, 100 / 69;
+// d = 200 47 / 44 at 500.  Binary16 storage gains at every size: d = 25 44 / 40 at
+// 500, 72 / 58 at 6500.  A Gaussian build is two launches longer, and a call that
+// lasts past about 50 us is woken some 15 us late, which the split one always is:
+// d = 25 39 / 65 at n = 500, 46 / 64 at 3000, 57 / 62 at 4500, 78 / 68 at 6500; d =
+// 128 46 / 65, 58 / 65, 70 / 65, 105 / 77; d = 200 57 / 62 at 2000, 71 / 65 at 3000;
+// d = 300 61 / 63 at 500, 66 / 62 at 2000 (binary16 the same).  Blocks of half the
+// rows and columns: linear, d = 25 29 / 32 at n = 500, 29 / 33 at 3000, 32 / 34 at
+// 4500, 38 / 39 at 6500, d = 66 32 / 33, 33 / 35, 38 / 37, 46 / 43; polynomial 32 / 32,
+// 33 / 33, 37 / 34, 42 / 39 and 36 / 33, 37 / 35, 43 / 37, 50 / 42; Gaussian 35 / 36,
+// 37 / 38, 40 / 40, 45 / 43 and 39 / 38, 40 / 40, 45 / 42, 53 / 46.  10 updates on the
+// fly, d = 25 to 64, 60 labels: 1377 / 1564 at n = 200, 763 / 805 at 1000, 714 / 726
+// at 2000; 2 labels 389 / 372, 427 / 423, 472 / 467; wider ones gain at every size
+// (d = 128, 60 labels 2458 / 1308 at 200).
+inline bool split_wanted(int64_t n, int d_pad, bool gauss, bool f16, bool onthefly, bool panel) {
+  if (d_pad < kSplitMinDpad) return false;
+  if (onthefly) return d_pad > 64 || n > 1024;
+  if (panel) return d_pad > 64 || n > 4096;
+  if (gauss) return d_pad > 256 || n > (d_pad > 128 ? 2048 : 4096);
+  return f16 || d_pad > 128 || n > 2048;
+}
+
 // Points per workgroup in the label/assign/scatter kernels.
 constexpr int kBlk = 256;
 

@@ -1,8 +1,8 @@
 """The K build on the binary16 matrix cores (each coordinate as two binary16 values).
 
 Sizes sit at the edges of its tiles: ragged last rows and columns, coordinate
-counts below, at and above its chunks of 16 (from 25 coordinates up), and one
-row tile more or less than the bands of eight its tiles are dealt in.
+counts below, at and above its chunks of 16 (from 25 coordinates up, where
+split_wanted's size rule takes it), and one row tile more or less than the bands of eight its tiles are dealt in.
 """
 import numpy as np
 import pytest
@@ -39,7 +39,8 @@ def _bound(X, d):
     return (2.0 ** -22 + 2.0 ** -23 + (3 * (d // 16 + 1) + 1) * 2.0 ** -24) * np.outer(nrm, nrm)
 
 
-CASES = [(1, 65), (127, 72), (128, 80), (129, 32), (257, 100), (300, 25), (385, 129), (1024, 49), (1025, 33)]
+CASES = [(1, 145), (127, 136), (128, 144), (129, 152), (2177, 32), (257, 164), (2100, 25), (385, 129), (1024, 161),
+         (2049, 49), (1025, 137), (2305, 33), (2051, 100)]
 
 
 @pytest.mark.parametrize("mode", ["packed", "resident"])
@@ -84,7 +85,7 @@ def test_a_norm_past_fp32_takes_the_fp32_build(kind, value):
     past fp32's range: the entries among the other points are as without it,
     and those with it are what fp32 products give."""
     _torch_cuda()
-    X = np.abs(_points(200, 70, 3, spread=False)) + np.float32(0.5)
+    X = np.abs(_points(200, 270, 3, spread=False)) + np.float32(0.5)
     Y = X.copy()
     Y[17, 4] = value
     with Engine(Y, kind, 0.01, mode="packed") as eng:
@@ -107,15 +108,15 @@ def test_without_room_for_the_split_points(mode):
     points: the build runs on the fp32 matrix cores, and iterating works."""
     _torch_cuda()
     from paper_2601_17136_amd import kkm
-    X = _points(700, 90, 5)
-    _, need = kkm.kkm_plan(700, 90, 9, kkm.KKM_LINEAR, 1 << 40, kkm.MODES[mode])
+    X = _points(700, 150, 5)
+    _, need = kkm.kkm_plan(700, 150, 9, kkm.KKM_LINEAR, 1 << 40, kkm.MODES[mode])
     ref = X.astype(np.float64) @ X.astype(np.float64).T
     nrm = np.sqrt(np.diag(ref))
     with Engine(X, "linear", mode=mode, mem_budget=need + 4096, k_hint=9) as eng:
         K = eng.K_rows()
         _, it, _ = eng.iterate(np.arange(700, dtype=np.int32) % 9, 9, 3)
         assert eng.info()["bytes_total"] <= need + 4096 and it == 3
-    assert np.all(np.abs(K - ref) <= 90 * 2.0 ** -24 * np.outer(nrm, nrm))
+    assert np.all(np.abs(K - ref) <= 150 * 2.0 ** -24 * np.outer(nrm, nrm))
 
 
 def test_the_split_points_give_way_to_scratch():
@@ -152,8 +153,8 @@ def _check_step(X, kind, g, c, p, cl, k, eng, oracle):
 
 
 @pytest.mark.parametrize("kind", ["gauss", "poly", "linear"])
-@pytest.mark.parametrize("n,d,k", [(1, 32, 1), (127, 25, 3), (128, 33, 2), (129, 48, 9), (300, 56, 40), (640, 64, 5),
-                                   (257, 65, 3), (700, 100, 30), (385, 130, 7)])
+@pytest.mark.parametrize("n,d,k", [(1, 32, 1), (1, 70, 1), (1025, 25, 3), (1152, 33, 2), (1153, 48, 9), (1300, 56, 40),
+                                   (1664, 64, 5), (127, 66, 3), (257, 65, 3), (700, 100, 30), (385, 130, 7)])
 def test_on_the_fly_step(oracle, n, d, k, kind):
     """Sweeps of two to four chunks held in LDS and of chunks staged per tile;
     blocks of one cluster and of several, ragged last tiles."""
@@ -174,7 +175,7 @@ def test_on_the_fly_fixups_and_small_budgets(oracle, d):
     exactly the budget kkm_plan asks for, which has no room for them."""
     _torch_cuda()
     from paper_2601_17136_amd import kkm
-    n, k = 500, 6
+    n, k = (1100 if d == 40 else 500), 6
     X = 0.3 * _points(n, d, 9, spread=False) + np.float32(20.0)
     cl = np.random.default_rng(1).integers(0, k, n).astype(np.int32)
     with Engine(X, "gauss", 0.05, mode="onthefly") as eng:
@@ -190,14 +191,15 @@ def test_on_the_fly_past_fp32_norms(d):
     """A point whose squared norm is past fp32's range: the other clusters'
     sums over the other points are finite and as without it."""
     _torch_cuda()
-    X = np.abs(_points(300, d, 3, spread=False)) + np.float32(0.5)
+    n = 1100 if d == 40 else 300
+    X = np.abs(_points(n, d, 3, spread=False)) + np.float32(0.5)
     X[17, 4] = 3e19
-    cl = (np.arange(300) % 3).astype(np.int32)
+    cl = (np.arange(n) % 3).astype(np.int32)
     cl[17] = 2
     with Engine(X, "linear", mode="onthefly") as eng:
         E = eng.step(cl, 3)["E"]
     X64 = X.astype(np.float64)
-    keep = np.arange(300) != 17
+    keep = np.arange(n) != 17
     for j in (0, 1):
         ref = X64[keep] @ X64[cl == j].sum(0)
         np.testing.assert_allclose(E[keep, j], ref, rtol=1e-5)
@@ -207,9 +209,9 @@ def test_on_the_fly_past_fp32_norms(d):
 @pytest.mark.parametrize("mode,d", [("packed", 25), ("packed", 54), ("packed", 301), ("resident", 784)])
 def test_diagonal_has_no_bias(mode, d):
     """tr K, and with it the objective, sees the mean error of the diagonal.  Rounded norms of random sign leave
-    2^-25 / sqrt(n) = 2^-30.5 of it at n = 2000; the bound is 2^-28 (a square without its lo lo is low by about 2^-25)."""
+    2^-25 / sqrt(n) = 2^-30.5 of it at n = 2100; the bound is 2^-28 (a square without its lo lo is low by about 2^-25)."""
     _torch_cuda()
-    X = np.random.default_rng(d).random((2000, d), dtype=np.float32)
+    X = np.random.default_rng(d).random((2100, d), dtype=np.float32)
     with Engine(X, "linear", mode=mode) as eng:
         K, diag = eng.K_rows(), eng.diag().astype(np.float64)
     ref = (X.astype(np.float64) ** 2).sum(1)
@@ -244,7 +246,7 @@ WIDE = [("one column", 1e6), ("one column", 1e8), ("one column", 1e12), ("two co
 
 
 @pytest.mark.parametrize("case,size", WIDE)
-@pytest.mark.parametrize("n,d", [(200, 32), (300, 130)])
+@pytest.mark.parametrize("n,d", [(2100, 32), (300, 130)])
 def test_rows_of_wide_range_keep_fp32_products(n, d, case, size):
     """Every entry within what fp32 products give, relative to the sum of its
     own terms' sizes (and not to the points' norms); K is the one that a budget
@@ -277,7 +279,7 @@ def test_rows_of_wide_range_on_the_fly(d, case, size):
     large points' entries over the small points' cluster."""
     torch = _torch_cuda()
     from paper_2601_17136_amd import kkm
-    n = 256
+    n = 1100 if d == 32 else 256
     X, big = _wide(case, n, d, size, d)
     cl = np.where(big, 0, 1).astype(np.int32)
     X64 = X.astype(np.float64)
@@ -306,10 +308,10 @@ def test_factors_at_the_ends_of_fp32(kind, gamma, scale):
     coordinate with the other half."""
     _torch_cuda()
     from paper_2601_17136_amd import kkm
-    n, d = 200, 40
+    n, d = 200, 280
     X = np.random.default_rng(8).random((n, d)).astype(np.float32) + np.float32(0.5)
-    X[: n // 2, 20:] = 0.0
-    X[n // 2:, :20] = 0.0
+    X[: n // 2, 140:] = 0.0
+    X[n // 2:, :140] = 0.0
     X *= np.float32(scale)
     args = (kind, gamma, 0.5, 1)
     with Engine(X, *args, mode="packed") as eng:
@@ -393,10 +395,10 @@ def test_on_the_fly_bits_do_not_depend_on_seeding(spare):
 def test_entries_have_no_bias(d):
     """Sums of K over a cluster, and the objective, see the mean error of its
     entries.  Roundings of random sign leave next to nothing of it over 4
-    million entries (the rows' own, 2^-25 over sqrt(d) and over sqrt(2000) rows,
+    million entries (the rows' own, 2^-25 over sqrt(d) and over sqrt(2100) rows,
     2^-33 at most); a turn of the sum's sign at the wrong chunk leaves 2e-9."""
     _torch_cuda()
-    X = np.random.default_rng(d).random((2000, d), dtype=np.float32)
+    X = np.random.default_rng(d).random((2100, d), dtype=np.float32)
     with Engine(X, "linear", mode="packed") as eng:
         K = eng.K_rows().astype(np.float64)
     ref = X.astype(np.float64) @ X.astype(np.float64).T
@@ -405,24 +407,32 @@ def test_entries_have_no_bias(d):
 
 
 @pytest.mark.parametrize("kind", ["linear", "poly", "gauss"])
-@pytest.mark.parametrize("n,d", [(1000, 70), (897, 33)])
+@pytest.mark.parametrize("n,d", [(1000, 270), (4225, 33), (1000, 70), (897, 33), (2050, 40)])
 def test_blocks_hold_the_bits_of_the_full_k(n, d, kind):
     """Entry (i, j) of any block is entry (i, j) of the full K, bit for bit, above,
     on and below the diagonal, ragged ends of rows and columns included; the
-    Gaussian with many entries recomputed."""
+    Gaussian with many entries recomputed.  (Blocks of few narrow points, whose
+    full K takes another kernel: of one block that holds everything.)"""
     torch = _torch_cuda()
     from paper_2601_17136_amd import kkm
     rng = np.random.default_rng(n)
     X = (rng.standard_normal((9, d))[rng.integers(0, 9, n)] + 0.05 * rng.standard_normal((n, d))).astype(np.float32)
     g, c, p = {"linear": (1.0, 0.0, 1), "poly": (0.5, 1.0, 3), "gauss": (20.0 / d, 0.0, 1)}[kind]
-    with Engine(X, kind, g, c, p, mode="resident") as eng:
-        K = eng.K_rows()
-        assert kind != "gauss" or eng.info()["fixups"] > n
-    assert np.array_equal(K, K.T)
     Xd = torch.from_numpy(X).cuda()
     ctx = kkm.kkm_create(kkm.current_stream_handle())
+    if d > 256 or n > 4096:
+        with Engine(X, kind, g, c, p, mode="resident") as eng:
+            K = eng.K_rows()
+            assert kind != "gauss" or eng.info()["fixups"] > n
+    else:
+        kkm.kkm_build_block(ctx, Xd, n, d, kkm.KINDS[kind], kkm.make_params(g, c, p), 0, n, 0, n)
+        out = torch.empty((n, n), device="cuda")
+        kkm.kkm_copy_kernel_rows(ctx, 0, n, out)
+        K = out.cpu().numpy()
+    assert np.array_equal(K, K.T)
     try:
-        for r0, r1, c0, c1 in [(0, n, 0, n), (128, n, 0, 700), (0, 300, 256, n), (256, 700, 128, 650), (640, n, 640, n),
+        for r0, r1, c0, c1 in [(0, n, 0, n), (n // 256 * 128, n, 0, n // 256 * 128), (128, n, 0, 700),
+                               (0, 300, 256, n), (256, 700, 128, 650), (640, n, 640, n),
                                (384, 400, 384, 500), (384, 500, 384, 400), (128, 129, 128, 129)]:
             kkm.kkm_build_block(ctx, Xd, n, d, kkm.KINDS[kind], kkm.make_params(g, c, p), r0, r1, c0, c1)
             out = torch.empty((r1 - r0, c1 - c0), device="cuda")
@@ -436,3 +446,39 @@ def test_blocks_hold_the_bits_of_the_full_k(n, d, kind):
             assert np.all(np.abs(E.cpu().numpy()[:, 0] - ref) <= 2.0 ** -24 * (r1 - r0 + 2) * scale)
     finally:
         kkm.kkm_destroy(ctx)
+
+
+@pytest.mark.parametrize("kind", ["linear", "poly", "gauss"])
+@pytest.mark.parametrize("layout,n,d", [("packed", 2048, 128), ("packed", 2049, 128), ("packed", 2049, 24),
+                                        ("packed", 700, 129), ("packed", 4096, 64), ("packed", 4097, 64),
+                                        ("packed", 2048, 200), ("packed", 2049, 200), ("packed", 300, 257),
+                                        ("resident16", 700, 33), ("resident16", 4097, 33), ("onthefly", 1024, 64),
+                                        ("onthefly", 1025, 64), ("block", 4096, 40), ("block", 4097, 40), ("block", 600, 65)])
+def test_both_sides_of_the_size_rule(layout, n, d, kind):
+    """The sizes at which the products change hands: E of a few clusters against 64 bits on either side."""
+    torch = _torch_cuda()
+    from paper_2601_17136_amd import kkm
+    X = _points(n, d, n + d, spread=False)
+    k, g = 5, 1.0 / d
+    cl = (np.arange(n) % k).astype(np.int32)
+    X64 = torch.from_numpy(X).cuda().double()
+    B = X64 @ X64.T
+    sq = B.diagonal()
+    K = B if kind == "linear" else (g * B + 1) ** 2 if kind == "poly" else torch.exp(-g * (sq[:, None] + sq[None] - 2 * B))
+    V = torch.nn.functional.one_hot(torch.from_numpy(cl).cuda().long(), k).double()
+    prm = (kind, g, 1.0 if kind == "poly" else 0.0, 2 if kind == "poly" else 1)
+    if layout == "block":
+        ctx = kkm.kkm_create(kkm.current_stream_handle())
+        E = torch.empty((n, k), device="cuda")
+        kkm.kkm_build_block(ctx, torch.from_numpy(X).cuda(), n, d, kkm.KINDS[kind], kkm.make_params(*prm[1:]), 0, n, 0, n)
+        kkm.kkm_block_spmm(ctx, torch.from_numpy(cl).cuda(), k, E)
+        kkm.kkm_destroy(ctx)
+        E = E.cpu().numpy()
+    else:
+        with Engine(X, *prm, mode=layout.replace("16", ""), storage="f16" if "16" in layout else "f32") as eng:
+            E = eng.step(cl, k)["E"]
+    ref = (K @ V).cpu().numpy()
+    scale = (K.abs() @ V).cpu().numpy()
+    # fp32 products and sums; binary16 entries carry 2^-11 and the row bound's share
+    assert np.all(np.abs(E - ref) <= (2.0 ** -10 if "16" in layout else 4e-6) * scale + (
+        2.0 ** -25 * n * np.abs(ref).max() if "16" in layout else 0.0))
