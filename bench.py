@@ -27,8 +27,9 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, 8 TB/s
 FP32_MFMA_PEAK_TF = 157.3    # MI355X dense fp32 matrix peak
-# From SPLIT_MIN_DPAD padded coordinates up the products run on the binary16
-# matrix cores (2.5 PFLOP/s dense), three of their products per fp32 one.
+# From SPLIT_MIN_DPAD padded coordinates up the products of these workloads (of
+# more than 4096 points there) run on the binary16 matrix cores (2.5 PFLOP/s
+# dense), three of their products per fp32 one.
 SPLIT_MFMA_PEAK_TF = 2500.0 / 3
 SPLIT_MIN_DPAD = 32
 METRIC = "clustering iters/sec + K-build TFLOP/s, % of HBM / MFMA peak, 1 GPU"
